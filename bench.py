@@ -88,7 +88,7 @@ def measured_traffic(config):
 
 # Every file of the convolution's translation unit: a change to any of them
 # can change the kernels the traffic counters were taken on.
-CONV_TU = ("oc_conv.hip", "oc_conv_gemm.inc", "oc_conv_bwd.inc", "oc_internal.h", "oc_device.h")
+CONV_TU = ("oc_conv.hip", "oc_conv_split.inc", "oc_conv_gemm.inc", "oc_conv_bwd.inc", "oc_internal.h", "oc_device.h")
 
 
 def conv_source_hash():

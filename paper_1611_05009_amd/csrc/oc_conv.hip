@@ -16,29 +16,6 @@
 
 #include "oc_internal.h"
 
-// Tuning knobs (compile-time): deltas of gathered A rows in flight in the
-// unit-voxel kernel; shell voxels / regions per scheduling group in the cell
-// kernels.
-#ifndef OC_UNIT_ACCS
-#define OC_UNIT_ACCS 1
-#endif
-#ifndef OC_UNIT_PREFETCH
-#define OC_UNIT_PREFETCH 2
-#endif
-// Deltas of gathers in flight where a lane's row piece is small (at most
-// OC_UNIT_SMALL_CH floats per lane per delta, so more deltas fit in
-// registers): the narrow layers are bound by the gathers, not by the
-// matrix unit.
-#ifndef OC_UNIT_PREFETCH_SMALL
-#define OC_UNIT_PREFETCH_SMALL 8
-#endif
-#ifndef OC_UNIT_SMALL_CH
-#define OC_UNIT_SMALL_CH 2
-#endif
-template <int CIN, int MS>
-constexpr int unit_prefetch() {
-  return CIN / (MS == 32 ? 2 : 4) <= OC_UNIT_SMALL_CH ? OC_UNIT_PREFETCH_SMALL : OC_UNIT_PREFETCH;
-}
 using namespace ocd;
 
 namespace {
@@ -724,193 +701,7 @@ __device__ __forceinline__ typename VecT<V>::type gather_at(const G& g, uint32_t
   return g.template load<V>(a, off);
 }
 
-#ifndef OC_UNIT_THREADS
-#define OC_UNIT_THREADS 512
-#endif
-constexpr int kUnitThreads = OC_UNIT_THREADS;
-
-template <int CIN, int NT, int MS, class GP>
-__global__ void __launch_bounds__(kUnitThreads) k_conv_unit_mfma(
-    int64_t n_leaves, const int32_t* __restrict__ nbt, const int64_t* __restrict__ n_groups,
-    const float* __restrict__ in, const float* __restrict__ wm, uint32_t n_rows,
-    const float* __restrict__ bias, int cout, int relu, float* __restrict__ out) {
-  // Channel blocks: blockIdx.y selects an output block (its weight layout
-  // and its [n_leaves][cout] destination).
-  wm += (int64_t)blockIdx.y * MfmaCfg<CIN, NT, MS>::WFLOATS;
-  out += (int64_t)blockIdx.y * n_leaves * cout;
-  if (bias != nullptr) bias += (int64_t)blockIdx.y * cout;
-  using C = MfmaCfg<CIN, NT, MS>;
-  const GP rin = GP::make(in, n_rows);
-  using Vec = typename VecT<C::VEC>::type;
-  using Acc = typename AccT<MS>::type;
-  extern __shared__ float smem[];
-  float* wl = smem;
-  int32_t* nb_all = reinterpret_cast<int32_t*>(smem + C::WFLOATS);
-  {
-    typedef float __attribute__((ext_vector_type(4))) f4;
-    const f4* src = reinterpret_cast<const f4*>(wm);
-    f4* dst = reinterpret_cast<f4*>(wl);
-    for (int i = threadIdx.x; i < C::WFLOATS / 4; i += blockDim.x) dst[i] = src[i];
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  // Two neighbourhood tables per wave: the current tile's, and the next
-  // tile's, which is staged between the MFMAs of this one.
-  int32_t* nb_w = nb_all + wave * (2 * C::GROUPS * 64);
-  const int64_t G = min(*n_groups, n_leaves / 8);
-  const int64_t n_tiles = (G + C::GROUPS - 1) / C::GROUPS;
-  const WaveTiles wt = wave_tiles(n_tiles);
-  // Lane roles.
-  const int m = lane % MS, g = lane / MS;
-  const int gi = m >> 3, o3 = m & 7;
-  const int ubase = gi * 64 + ((o3 >> 2) & 1) * 16 + ((o3 >> 1) & 1) * 4 + (o3 & 1);
-  const int col = lane % MS;
-  // The neighbourhood rows of tile t: loaded from the table (one coalesced
-  // load per group) well before they are needed, then written to the LDS
-  // table of the wave.
-  int32_t tbl[C::GROUPS];
-  auto stage_load = [&](int64_t t) {
-#pragma unroll
-    for (int q = 0; q < C::GROUPS; ++q) {
-      const int64_t gidx = t * C::GROUPS + q;
-      tbl[q] = (t < wt.end && gidx < G) ? nbt[gidx * 64 + lane] : -1;
-    }
-  };
-  auto stage_rows = [&](int32_t* nbl) {
-#pragma unroll
-    for (int q = 0; q < C::GROUPS; ++q) nbl[q * 64 + lane] = tbl[q];
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  };
-  // The lane's bias values, read once (a load in the epilogue would make it
-  // wait for the next tile's gathers as well).
-  float bvals[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int co = MS * nt + col;
-    bvals[nt] = (bias != nullptr && co < cout) ? bias[co] : 0.f;
-  }
-  // Epilogue of a finished tile (unit cells need no 1/s^3 scaling).
-  auto store_unit_tile = [&](const Acc (&res)[NT], const int32_t* tnb) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int co = MS * nt + col;
-      const float bv = bvals[nt];
-#pragma unroll
-      for (int r = 0; r < (MS == 32 ? 16 : 4); ++r) {
-        const int i = MS == 32 ? 8 * (r / 4) + 4 * g + (r % 4) : 4 * g + r;
-        const int row0 = tnb[(i >> 3) * 64 + 21];  // voxel (1,1,1): first row of the group
-        if (row0 < 0 || row0 + 8 > n_leaves || co >= cout) continue;
-        float v = res[nt][r] + bv;
-        if (relu & 1) v = fmaxf(v, 0.f);
-        out[(int64_t)(row0 + (i & 7)) * cout + co] = v;
-      }
-    }
-  };
-  // Software pipeline: the gathered A rows of delta dl+PD and the B operands
-  // of delta dl+1 are in flight while the MFMAs of delta dl issue; the
-  // gathers of a tile's first PD deltas are issued during the previous
-  // tile's last ones (PD + 1 divides 27, so the buffer ring lines up).  The
-  // scheduling barriers keep the compiler from sinking the loads back to
-  // their use.
-  constexpr int PD = unit_prefetch<CIN, MS>();  // deltas of gathers in flight
-  static_assert(27 % (PD + 1) == 0, "the gather ring must line up across tiles");
-  Vec abuf[PD + 1][C::NV];
-  const uint32_t coff = 4u * C::VEC * g;  // the lane's first channel, in bytes
-  auto gather_row = [&](uint32_t row, Vec* a) {
-#pragma unroll
-    for (int v = 0; v < C::NV; ++v) a[v] = gather_at<C::VEC>(rin, row, coff + 4 * C::VSTRIDE * v);
-  };
-  // The lane's A rows for the first PD deltas of a table.
-  uint32_t noff[PD];
-  auto first_offsets = [&](const int32_t* t) {
-#pragma unroll
-    for (int k = 0; k < PD; ++k) noff[k] = GP::addr(t[ubase + (k / 9) * 16 + ((k / 3) % 3) * 4 + k % 3]);
-  };
-  // A finished tile is stored during the next tile's fifth delta: its stores
-  // then queue behind gathers that are already consumed, and the gathers
-  // issued after them are consumed deltas later (the memory counter is
-  // in issue order).
-  Acc pacc[NT];
-  const int32_t* pnb = nb_w;
-  bool have_prev = false;
-  int cur = 0;
-  stage_load(wt.first);
-  stage_rows(nb_w);
-  first_offsets(nb_w);
-#pragma unroll
-  for (int k = 0; k < PD; ++k) gather_row(noff[k], abuf[k]);
-  for (int64_t tile = wt.first; tile < wt.end; tile += wt.stride) {
-    int32_t* nb = nb_w + cur * (C::GROUPS * 64);
-    int32_t* nb_next = nb_w + (cur ^ 1) * (C::GROUPS * 64);
-    const int64_t next = tile + wt.stride;
-    // OC_UNIT_ACCS independent accumulator sets (deltas alternate between
-    // them) so that consecutive MFMAs do not wait on each other's results.
-    constexpr int NA = OC_UNIT_ACCS;
-    Acc acc2[NA][NT];
-#pragma unroll
-    for (int a2 = 0; a2 < NA; ++a2)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int r = 0; r < (MS == 32 ? 16 : 4); ++r) acc2[a2][nt][r] = 0.f;
-    Vec bbuf[2][NT][C::NV];
-    // The 27 A rows of this lane, read from the table up front so that no
-    // LDS round trip sits between a delta's MFMAs and its gathers.
-    uint32_t aoff[27];
-#pragma unroll
-    for (int dl = 0; dl < 27; ++dl) aoff[dl] = GP::addr(nb[ubase + (dl / 9) * 16 + ((dl / 3) % 3) * 4 + dl % 3]);
-    auto load_b = [&](int dl, Vec (*b)[C::NV]) {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const Vec* bsrc = reinterpret_cast<const Vec*>(wl) + ((dl * NT + nt) * C::NV) * 64 + lane;
-#pragma unroll
-        for (int v = 0; v < C::NV; ++v) b[nt][v] = bsrc[v * 64];
-      }
-    };
-    load_b(0, bbuf[0]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int dl = 0; dl < 27; ++dl) {
-      if (dl + PD < 27) gather_row(aoff[dl + PD], abuf[(dl + PD) % (PD + 1)]);
-      else gather_row(noff[dl + PD - 27], abuf[(dl + PD) % (PD + 1)]);  // next tile
-      if (dl + 1 < 27) load_b(dl + 1, bbuf[(dl + 1) % 2]);
-      // The next tile's neighbourhood rows.
-      if (dl == 3) stage_load(next);
-      if (dl == 4 && have_prev) store_unit_tile(pacc, pnb);
-      if (dl == 18) {
-        stage_rows(nb_next);
-        first_offsets(nb_next);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int v = 0; v < C::NV; ++v)
-#pragma unroll
-          for (int e = 0; e < C::VEC; ++e)
-            acc2[(v * C::VEC + e) % NA][nt] =
-                mfma<MS>(vget<C::VEC>(abuf[dl % (PD + 1)][v], e),
-                         vget<C::VEC>(bbuf[dl % 2][nt][v], e), acc2[(v * C::VEC + e) % NA][nt]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    Acc acc[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      acc[nt] = acc2[0][nt];
-#pragma unroll
-      for (int a2 = 1; a2 < NA; ++a2) acc[nt] += acc2[a2][nt];
-    }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) pacc[nt] = acc[nt];
-    pnb = nb;
-    have_prev = true;
-    cur ^= 1;
-    __builtin_amdgcn_wave_barrier();  // nb is rewritten by the next tile
-  }
-  if (have_prev) store_unit_tile(pacc, pnb);
-}
+#include "oc_conv_split.inc"
 
 // ---------------------------------------------------------------------------
 // MFMA kernels for cells of edge 2, 4 and 8.
@@ -2441,183 +2232,6 @@ __global__ void __launch_bounds__(kCellrThreads) k_conv_cellr_mfma(
                                                       kpre, t0, t1);
 }
 
-// Edge-8 cells whose face and edge neighbour trees are unsplit.  Every shell
-// region is then one leaf's row (corners always are), so
-// S_delta = sum_r w(delta, r) x_r over the cell's own row (r = 13) and its 26
-// region rows, w(delta, r) being the number of region r's voxels in the
-// window of delta, and Eq. 8 becomes out = b + sum_r W8_r x_r with effective
-// weights W8_r = (1/512) sum_delta w(delta, r) W[1 - delta], formed once per
-// weight set.  That is the unit voxels' gather-GEMM (K = 27 cin): MS cells
-// per tile, term r's rows gathered into the A operand two terms ahead, the
-// next tile's term rows loaded during this one.
-template <int CIN, int NT, int MS, class GP>
-__global__ void __launch_bounds__(kUnitThreads) k_conv_cell8t_gemm(
-    int64_t n_leaves, const int32_t* __restrict__ brow, const int64_t* __restrict__ meta,
-    const int32_t* __restrict__ codes, int64_t ccap, const float* __restrict__ in,
-    const float* __restrict__ wm, uint32_t n_rows, const float* __restrict__ bias, int cout,
-    int relu, float* __restrict__ out) {
-  // Channel blocks: blockIdx.y selects an output block (its weight layout
-  // and its [n_leaves][cout] destination).
-  wm += (int64_t)blockIdx.y * MfmaCfg<CIN, NT, MS>::WFLOATS;
-  out += (int64_t)blockIdx.y * n_leaves * cout;
-  if (bias != nullptr) bias += (int64_t)blockIdx.y * cout;
-  using C = MfmaCfg<CIN, NT, MS>;
-  using Vec = typename VecT<C::VEC>::type;
-  using Acc = typename AccT<MS>::type;
-  const GP rin = GP::make(in, n_rows);
-  extern __shared__ float smem[];
-  float* wl = smem;
-  weights_to_lds<CIN, NT, MS>(wm, wl);
-  const int lane = threadIdx.x & 63;
-  const int m = lane % MS, g = lane / MS, col = lane % MS;
-  int64_t cnt = meta[0];  // the kind comes first in the lists
-  if (cnt > ccap) cnt = ccap;
-  if (cnt > n_leaves) cnt = n_leaves;
-  const WaveTiles wt = wave_tiles((cnt + MS - 1) / MS);
-  float bvals[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int co = MS * nt + col;
-    bvals[nt] = (bias != nullptr && co < cout) ? bias[co] : 0.f;
-  }
-  // Term rows of the lane's cell in tile t (-1: none).
-  int32_t trow[27];
-  auto stage_load = [&](int64_t t) {
-    const int64_t idx = t * MS + m;
-    const bool ok = t < wt.end && idx < cnt;
-#pragma unroll
-    for (int r = 0; r < 27; ++r) {
-      int32_t v = -1;
-      if (ok) v = r == 13 ? brow[idx] : codes[(int64_t)(r - (r > 13)) * ccap + idx];
-      trow[r] = v < n_leaves ? v : -1;  // only a non-canonical structure exceeds
-    }
-  };
-  auto store_tile = [&](const Acc (&res)[NT], int srow) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int co = MS * nt + col;
-#pragma unroll
-      for (int r = 0; r < (MS == 32 ? 16 : 4); ++r) {
-        const int i = MS == 32 ? 8 * (r / 4) + 4 * g + (r % 4) : 4 * g + r;
-        const int rowi = __shfl(srow, i, 64);
-        if (rowi < 0 || co >= cout) continue;
-        float v = fmaf(res[nt][r], (relu & 2) ? 512.f : 1.f, bvals[nt]);
-        if (relu & 1) v = fmaxf(v, 0.f);
-        out[(int64_t)rowi * cout + co] = v;
-      }
-    }
-  };
-  constexpr int PD = unit_prefetch<CIN, MS>();
-  static_assert(27 % (PD + 1) == 0, "the gather ring must line up across tiles");
-  Vec abuf[PD + 1][C::NV];
-  const uint32_t coff = 4u * C::VEC * g;  // the lane's first channel, in bytes
-  auto gather_row = [&](uint32_t row, Vec* a) {
-#pragma unroll
-    for (int v = 0; v < C::NV; ++v) a[v] = gather_at<C::VEC>(rin, row, coff + 4 * C::VSTRIDE * v);
-  };
-  uint32_t aoff[27];
-  auto offsets = [&]() {
-#pragma unroll
-    for (int r = 0; r < 27; ++r) aoff[r] = GP::addr(trow[r]);
-  };
-  Acc pacc[NT];
-  int psrow = -1;
-  bool have_prev = false;
-  stage_load(wt.first);
-  offsets();
-#pragma unroll
-  for (int k = 0; k < PD; ++k) gather_row(aoff[k], abuf[k]);
-  for (int64_t tile = wt.first; tile < wt.end; tile += wt.stride) {
-    const int srow = trow[13];
-    Vec bbuf[2][NT][C::NV];
-    auto load_b = [&](int dl, Vec (*b)[C::NV]) {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const Vec* bsrc = reinterpret_cast<const Vec*>(wl) + ((dl * NT + nt) * C::NV) * 64 + lane;
-#pragma unroll
-        for (int v = 0; v < C::NV; ++v) b[nt][v] = bsrc[v * 64];
-      }
-    };
-    Acc acc[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int r = 0; r < (MS == 32 ? 16 : 4); ++r) acc[nt][r] = 0.f;
-    load_b(0, bbuf[0]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int dl = 0; dl < 27; ++dl) {
-      if (dl + PD < 27) gather_row(aoff[dl + PD], abuf[(dl + PD) % (PD + 1)]);
-      else gather_row(aoff[dl + PD - 27], abuf[(dl + PD) % (PD + 1)]);  // next tile
-      if (dl + 1 < 27) load_b(dl + 1, bbuf[(dl + 1) % 2]);
-      if (dl == 3) stage_load(tile + wt.stride);
-      if (dl == 4 && have_prev) store_tile(pacc, psrow);
-      if (dl == 22) {
-        // The next tile's offsets (this tile's are no longer needed past
-        // the gathers already issued).
-#pragma unroll
-        for (int k = 0; k < PD; ++k) aoff[k] = GP::addr(trow[k]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int v = 0; v < C::NV; ++v)
-#pragma unroll
-          for (int e = 0; e < C::VEC; ++e)
-            acc[nt] = mfma<MS>(vget<C::VEC>(abuf[dl % (PD + 1)][v], e),
-                               vget<C::VEC>(bbuf[dl % 2][nt][v], e), acc[nt]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) pacc[nt] = acc[nt];
-    psrow = srow;
-    have_prev = true;
-    offsets();  // the next tile's
-  }
-  if (have_prev) store_tile(pacc, psrow);
-}
-
-// Effective weights of the edge-8 gather-GEMM, in the unit kernel's B-operand
-// order: term r (region dir = (r/9 - 1, (r/3)%3 - 1, r%3 - 1), r = 13 the cell
-// itself) takes (1/sz^3) sum_delta w(delta, r) W[tap 1 - delta], where
-// w(delta, r) = 0 unless delta_a = dir_a wherever dir_a != 0, and is the
-// product of sz - |delta_a| over the other axes.
-template <int CIN, int NT, int MS>
-__global__ void k_eff_weights(const float* __restrict__ w, int cout, int sz,
-                              float* __restrict__ wm) {
-  using C = MfmaCfg<CIN, NT, MS>;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= C::WFLOATS) return;
-  // Channel blocks: blockIdx.y selects a [cout][CIN][27] weight block.
-  w += (int64_t)blockIdx.y * cout * CIN * 27;
-  wm += (int64_t)blockIdx.y * C::WFLOATS;
-  int q = idx;
-  const int e = q % C::VEC; q /= C::VEC;
-  const int lane = q % 64; q /= 64;
-  const int jv = q % C::NV; q /= C::NV;
-  const int nt = q % NT; q /= NT;
-  const int r = q;
-  const int co = MS * nt + lane % MS;
-  const int ci = C::VEC * (C::KS * jv + lane / MS) + e;
-  if (co >= cout) {
-    wm[idx] = 0.f;
-    return;
-  }
-  const int dir[3] = {r / 9 - 1, (r / 3) % 3 - 1, r % 3 - 1};
-  double acc = 0.0;
-  for (int dl = 0; dl < 27; ++dl) {
-    const int dlt[3] = {dl / 9 - 1, (dl / 3) % 3 - 1, dl % 3 - 1};
-    int wgt = 1;
-    for (int a = 0; a < 3; ++a) {
-      if (dir[a] != 0) wgt *= dlt[a] == dir[a] ? 1 : 0;
-      else wgt *= sz - (dlt[a] != 0 ? 1 : 0);
-    }
-    if (wgt != 0) acc += (double)wgt * (double)w[((int64_t)co * CIN + ci) * 27 + (26 - dl)];
-  }
-  wm[idx] = (float)(acc / ((double)sz * sz * sz));
-}
-
 // Weights in B-operand order: for delta index dl, N-tile nt, vector jv, lane
 // and element e: column co = MS*nt + lane%MS, channel ci = VEC*(KS*jv +
 // lane/MS) + e, tap 26 - dl (Eq. 7 pairs input offset delta with tap 1 - delta).
@@ -2643,88 +2257,75 @@ __global__ void k_mfma_weights(const float* __restrict__ w, int cout, float* __r
 // ---------------------------------------------------------------------------
 // Instantiated channel pairs.
 // ---------------------------------------------------------------------------
-typedef void (*MfmaFn)(int64_t, const int32_t*, const int64_t*, const float*, const float*,
-                       uint32_t, const float*, int, int, float*);
+typedef void (*UnitFn)(int64_t, const int32_t*, const int64_t*, const float*, const u32x4*, const int32_t*,
+                       PlainWeights, uint32_t, const float*, int, int, float*);
 typedef void (*CellFn)(const uint32_t*, const int64_t*, int, int, int, int64_t, const uint64_t*,
                        const int32_t*, const int64_t*, int, const int32_t*, const float*, const int64_t*,
                        int64_t, int64_t, const float*, const float*, uint32_t, const float*, int, int, float*,
                        const int64_t*, int64_t, int64_t);
 typedef void (*WeightFn)(const float*, int, float*);
-typedef void (*Cell8Fn)(int64_t, const int32_t*, const int64_t*, const int32_t*, int64_t,
-                        const float*, const float*, uint32_t, const float*, int, int, float*);
+typedef void (*Cell8Fn)(int64_t, const int32_t*, const int64_t*, const int32_t*, int64_t, const float*,
+                        const u32x4*, const int32_t*, PlainWeights, uint32_t, const float*, int, int, float*);
 typedef void (*Cell2Fn)(int64_t, const int32_t*, const int32_t*, const int32_t*, int64_t, const int64_t*,
                         const float*, const float*, uint32_t, const float*, int, int, float*);
-typedef void (*EffWeightFn)(const float*, int, int, float*);
+typedef void (*SplitWeightFn)(const float*, int, int, int, const float*, int, u32x4*, int32_t*, u32x4*, int32_t*);
 typedef void (*SumFn)(const uint32_t*, const int64_t*, const int32_t*, const int64_t*,
                       const int64_t*, int64_t, int64_t, const float*, uint32_t, float*,
                       const int64_t*, const int64_t*, int64_t, int64_t, const uint32_t*);
 
 struct MfmaVariant {
-  int cin, cout_max, cout_min, ms, nt;
-  size_t wfloats;       // unit-voxel kernel weights (MS-row tiles)
-  WeightFn weights;
-  size_t cell_wfloats;  // cell kernels' weights (16-row tiles)
+  int cin, cout_max, cout_min;
+  size_t split_bytes;      // split weights of a gather-GEMM (unit voxels, edge-8 cells)
+  int unit_smem, cell8g_smem;  // their kernels' LDS bytes
+  int unit_per_cu;         // workgroups per CU of the unit-voxel kernel
+  SplitWeightFn split_weights;
+  size_t cell_wfloats;     // cell kernels' weights (16-row tiles)
   WeightFn cell_weights;
-  EffWeightFn eff_weights; // edge-8 effective weights (unit-kernel layout)
   // The kernels, [0] gathering through RowsRaw (input below 4 GiB), [1]
   // through RowsWide.
-  MfmaFn kernel[2];
+  UnitFn unit[2];
   Cell2Fn cell2[2];
   CellFn cell4[2], cell8[2];
   SumFn sums[2];
-  Cell8Fn cell8g[2];    // edge-8 cells with unsplit face/edge neighbours
+  Cell8Fn cell8g[2];       // edge-8 cells with unsplit face/edge neighbours
 };
 
-template <int CIN, int NT, int MS, int WIDE>
+template <int CIN, int CNT, int WIDE>
 void set_kernels(MfmaVariant& v) {
-  using C = MfmaCfg<CIN, NT, MS>;
-  constexpr int CNT = (C::NCOL + 15) / 16;
   using G = typename std::conditional<WIDE != 0, RowsWide<CIN>, RowsRaw<CIN>>::type;
-  v.kernel[WIDE] = &k_conv_unit_mfma<CIN, NT, MS, G>;
+  v.unit[WIDE] = &k_conv_unit_split<CIN, G>;
   v.cell2[WIDE] = &k_conv_cell2_mfma<CIN, CNT, G>;
   v.cell4[WIDE] = &k_conv_cellr_mfma<CIN, CNT, 4, false, G>;
   v.cell8[WIDE] = &k_conv_cellr_mfma<CIN, CNT, 8, false, G>;
   v.sums[WIDE] = &k_boundary_sums<CIN, G>;
-  v.cell8g[WIDE] = &k_conv_cell8t_gemm<CIN, NT, MS, G>;
+  v.cell8g[WIDE] = &k_conv_cell8t_split<CIN, G>;
 }
 
-template <int CIN, int NT, int MS>
+// CNT: 16-column tiles of the cell kernels.
+template <int CIN, int CNT>
 MfmaVariant make_variant(int cout_min) {
-  using C = MfmaCfg<CIN, NT, MS>;
   MfmaVariant v;
   v.cin = CIN;
-  v.cout_max = C::NCOL;
+  v.cout_max = 16 * CNT;
   v.cout_min = cout_min;
-  v.ms = MS;
-  v.nt = NT;
-  v.wfloats = C::WFLOATS;
-  v.weights = &k_mfma_weights<CIN, NT, MS>;
-  constexpr int CNT = (C::NCOL + 15) / 16;
+  v.split_bytes = SplitCfg<CIN>::WBYTES;
+  v.unit_smem = SplitCfg<CIN>::SMEM;
+  v.cell8g_smem = cell8t_smem<CIN>();
+  v.unit_per_cu = SplitCfg<CIN>::PER_CU;
+  v.split_weights = &k_split_weights<CIN>;
   v.cell_wfloats = MfmaCfg<CIN, CNT, 16>::WFLOATS;
   v.cell_weights = &k_mfma_weights<CIN, CNT, 16>;
-  v.eff_weights = &k_eff_weights<CIN, NT, MS>;
-  set_kernels<CIN, NT, MS, 0>(v);
-  set_kernels<CIN, NT, MS, 1>(v);
+  set_kernels<CIN, CNT, 0>(v);
+  set_kernels<CIN, CNT, 1>(v);
   return v;
 }
 
-// cout in [cout_min, cout_max]; 32-wide tiles for cout 17..32, 16-wide ones
-// for cout 1..16 (a tile column past cout holds zero weights and is not
-// stored).
-#ifndef OC_NARROW_COUT_MIN
-#define OC_NARROW_COUT_MIN 1
-#endif
+// cout in [cout_min, cout_max] (a tile column past cout holds zero weights
+// and is not stored).
 const MfmaVariant* find_variant(int cin, int cout) {
   static const MfmaVariant table[] = {
-#ifdef OC_UNIT_MS16
-      make_variant<32, 2, 16>(17), make_variant<16, 2, 16>(17), make_variant<8, 2, 16>(17),
-      make_variant<4, 2, 16>(17),
-#else
-      make_variant<32, 1, 32>(17), make_variant<16, 1, 32>(17), make_variant<8, 1, 32>(17),
-      make_variant<4, 1, 32>(17),
-#endif
-      make_variant<32, 1, 16>(OC_NARROW_COUT_MIN),  make_variant<16, 1, 16>(OC_NARROW_COUT_MIN),
-      make_variant<8, 1, 16>(OC_NARROW_COUT_MIN),   make_variant<4, 1, 16>(OC_NARROW_COUT_MIN),
+      make_variant<32, 2>(17), make_variant<16, 2>(17), make_variant<8, 2>(17), make_variant<4, 2>(17),
+      make_variant<32, 1>(1),  make_variant<16, 1>(1),  make_variant<8, 1>(1),  make_variant<4, 1>(1),
   };
   for (const MfmaVariant& v : table)
     if (v.cin == cin && cout >= v.cout_min && cout <= v.cout_max) return &v;
@@ -2812,8 +2413,11 @@ __global__ void k_block_accum(const float* __restrict__ part, int K, int cb, int
 #endif
 constexpr int kSumChunks = OC_SUM_CHUNKS;
 
+// LDS bytes of the widest of a variant's kernels.
 size_t mfma_smem(const MfmaVariant& v) {
-  return sizeof(float) * v.wfloats + sizeof(int32_t) * (kUnitThreads / 64) * 2 * (v.ms / 8) * 64;
+  const size_t gather = v.unit_smem > v.cell8g_smem ? v.unit_smem : v.cell8g_smem;
+  const size_t cells = sizeof(float) * v.cell_wfloats + (size_t)(kMfmaThreads / 64) * kShell2Lds;
+  return gather > cells ? gather : cells;
 }
 
 // Compute units and LDS bytes per workgroup of the current device, queried
@@ -2862,9 +2466,10 @@ size_t smem_limit() {
 // Workspace layout (each part 256-byte aligned):
 //   leaf_info  u64 [n_leaves]                written by execute, for the generic and GEMM paths
 //   wt         f32 [27 cin cout]            generic-kernel weights
-//   wm         f32 [variant wfloats]        unit-voxel kernel B operands (if a variant exists)
+//   u16, uexp  [variant split_bytes], i32 [32]  split weights of the unit-voxel kernel (if a variant exists)
 //   wc         f32 [variant cell_wfloats]   cell kernels' B operands
-//   w8         f32 [variant wfloats]        edge-8 effective weights (unit layout)
+//   w8         f32 [27 cin cout]            edge-8 effective weights, [27][cin][cout] per block
+//   e16, eexp                               the same, split
 //   6 x (scan workspace (n_trees), i64 [n_trees + 1])
 //              per tree: unit groups, each kind of larger cell, boundary-sum
 //              slots -> prefixes
@@ -2896,9 +2501,12 @@ constexpr int kNodeScan = 2 + kKinds;
 struct ConvWs {
   uint64_t* info;
   float* wt;
-  float* wm;
+  u32x4* u16;
+  int32_t* uexp;
   float* wc;
   float* w8;
+  u32x4* e16;
+  int32_t* eexp;
   char* scan[kScans];
   int64_t* pre[kScans];
   int64_t* gkey;
@@ -2953,9 +2561,12 @@ ConvWs carve(void* base, int64_t n_trees, int64_t n_leaves, int cin, int cout, i
   if (!v) v = bl.v;
   w.info = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * (size_t)n_leaves));
   w.wt = reinterpret_cast<float*>(take(sizeof(float) * 27 * (size_t)cin * cout));
-  w.wm = reinterpret_cast<float*>(take(v ? sizeof(float) * v->wfloats * nwl : 0));
+  w.u16 = reinterpret_cast<u32x4*>(take(v ? v->split_bytes * nwl : 0));
+  w.uexp = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * 32 * nwl));
   w.wc = reinterpret_cast<float*>(take(v ? sizeof(float) * v->cell_wfloats * nwl : 0));
-  w.w8 = reinterpret_cast<float*>(take(v ? sizeof(float) * v->wfloats * nwl : 0));
+  w.w8 = reinterpret_cast<float*>(take(v ? sizeof(float) * 27 * (size_t)cin * cout : 0));
+  w.e16 = reinterpret_cast<u32x4*>(take(v ? v->split_bytes * nwl : 0));
+  w.eexp = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * 32 * nwl));
   for (int k = 0; k < kScans; ++k) {
     w.scan[k] = take(oci::scan_workspace(n_trees));
     w.pre[k] = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * (size_t)(n_trees + 1)));
@@ -3031,9 +2642,13 @@ __global__ void k_zero_u64(unsigned long long* p) { *p = 0ull; }
 // bit 1 writes each cell's sum over its voxels instead of their mean (the
 // bias still added once).
 struct FusedOut {
-  const float* wm;
+  const u32x4* u16;
+  const int32_t* uexp;
+  PlainWeights uw;
+  const u32x4* e16;
+  const int32_t* eexp;
+  PlainWeights ew;
   const float* wc;
-  const float* w8;
   const float* bias;
   int cout, relu;
   float* out;
@@ -3059,17 +2674,13 @@ hipError_t fused_pass(const oci::ConvArgs& a, const ConvWs& w, const MfmaVariant
   // edge-4/8 kernels pick their boundary sums' policy on the device).
   const int wide = (uint64_t)n_rows * (uint64_t)v->cin * 4u >= (uint64_t)kOutside ? 1 : 0;
   const size_t wsmem = sizeof(float) * v->cell_wfloats;
-  const size_t msmem = mfma_smem(*v);
-  if (msmem > max_smem) return hipErrorInvalidConfiguration;
+  if (mfma_smem(*v) > max_smem) return hipErrorInvalidConfiguration;
   const int nblk = ((num_cus + 7) / 8) * 8;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(v->kernel[wide]),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)msmem);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(v->unit[wide]),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, v->unit_smem);
   if (e != hipSuccess) return e;
-  // Edge-8 cells with unsplit face and edge neighbours: the gather-GEMM with
-  // effective weights (same LDS footprint as the unit kernel, no tables).
-  const size_t gsm = sizeof(float) * v->wfloats;
   e = hipFuncSetAttribute(reinterpret_cast<const void*>(v->cell8g[wide]),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)gsm);
+                          hipFuncAttributeMaxDynamicSharedMemorySize, v->cell8g_smem);
   if (e != hipSuccess) return e;
   auto launch_cells = [&](int k, int64_t t0, int64_t t1) -> hipError_t {
     const size_t smem = wsmem;
@@ -3086,14 +2697,14 @@ hipError_t fused_pass(const oci::ConvArgs& a, const ConvWs& w, const MfmaVariant
                        (const int64_t*)w.pre[1 + k], t0, t1);
     return hipGetLastError();
   };
-  hipLaunchKernelGGL(v->kernel[wide], dim3(nblk, nk), dim3(kUnitThreads), msmem, s, a.n_leaves,
-                     (const int32_t*)w.nbt, (const int64_t*)(w.pre[0] + a.n_trees), in, o.wm, n_rows,
+  hipLaunchKernelGGL(v->unit[wide], dim3(nblk * v->unit_per_cu, nk), dim3(kSplitThreads), v->unit_smem, s, a.n_leaves,
+                     (const int32_t*)w.nbt, (const int64_t*)(w.pre[0] + a.n_trees), in, o.u16, o.uexp, o.uw, n_rows,
                      o.bias, o.cout, o.relu, o.out);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(v->cell8g[wide], dim3(nblk, nk), dim3(kUnitThreads), gsm, s, a.n_leaves,
+  hipLaunchKernelGGL(v->cell8g[wide], dim3(2 * nblk, nk), dim3(kSplitThreads), v->cell8g_smem, s, a.n_leaves,
                      (const int32_t*)w.brow, (const int64_t*)w.meta, (const int32_t*)w.codes, w.ccap, in,
-                     o.w8, n_rows, o.bias, o.cout, o.relu, o.out);
+                     o.e16, o.eexp, o.ew, n_rows, o.bias, o.cout, o.relu, o.out);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // Edge-2 cells (no boundary sums); the kernel keeps the shell offsets of
@@ -3209,12 +2820,12 @@ hipError_t launch_conv_prepare(const ConvArgs& a, void* ws, hipStream_t s) {
       wcout = bl.cb;
       nb = (unsigned)(bl.J * bl.K);
     }
-    hipLaunchKernelGGL(v->weights, dim3((unsigned)((v->wfloats + 255) / 256), nb), dim3(256), 0, s,
-                       wsrc, wcout, w.wm);
     hipLaunchKernelGGL(v->cell_weights, dim3((unsigned)((v->cell_wfloats + 255) / 256), nb), dim3(256), 0,
                        s, wsrc, wcout, w.wc);
-    hipLaunchKernelGGL(v->eff_weights, dim3((unsigned)((v->wfloats + 255) / 256), nb), dim3(256), 0, s,
-                       wsrc, wcout, 8, w.w8);
+    hipLaunchKernelGGL(k_eff_weights, dim3((unsigned)((27 * v->cin * wcout + 255) / 256), nb), dim3(256), 0, s, wsrc,
+                       v->cin, wcout, w.w8);
+    hipLaunchKernelGGL(v->split_weights, dim3(28, nb, 2), dim3(256), 0, s, (const float*)w.wt, a.cin, a.cout,
+                       a.cout / wcout, (const float*)w.w8, wcout, w.u16, w.uexp, w.e16, w.eexp);
   }
   const unsigned tb = (unsigned)((a.n_trees + 255) / 256);
   hipLaunchKernelGGL(k_leaf_kinds, dim3(tb), dim3(256), 0, s, a.trees, a.n_trees, a.gd, a.gh, a.gw,
@@ -3311,7 +2922,8 @@ hipError_t launch_conv_execute(const ConvArgs& a, void* ws, int impl, hipStream_
   if (e != hipSuccess) return e;
   const int num_cus = L.num_cus;
   if (v != nullptr) {
-    const FusedOut o{w.wm, w.wc, w.w8, a.bias, a.cout, a.relu | (a.sum_cells ? 2 : 0), a.out};
+    const FusedOut o{w.u16,  w.uexp, PlainWeights{w.wt, a.cin, a.cout}, w.e16, w.eexp,
+                     PlainWeights{w.w8, a.cin, a.cout}, w.wc, a.bias, a.cout, a.relu | (a.sum_cells ? 2 : 0), a.out};
     return fused_pass(a, w, v, a.in, n_rows, o, 1, L, s);
   }
   // Channel blocks: per input block j (copied to a dense [n_leaves][32]
@@ -3330,8 +2942,11 @@ hipError_t launch_conv_execute(const ConvArgs& a, void* ws, int impl, hipStream_
     }
     // The K output blocks of input block j in one grid (rows k).
     const size_t b = (size_t)j * bl.K;
-    const FusedOut o{w.wm + b * bl.v->wfloats, w.wc + b * bl.v->cell_wfloats, w.w8 + b * bl.v->wfloats,
-                     nullptr, bl.cb, a.sum_cells ? 2 : 0, w.part};
+    const FusedOut o{w.u16 + b * (bl.v->split_bytes / 16), w.uexp + b * 32,
+                     PlainWeights{w.wt + (size_t)j * 32 * a.cout, a.cin, a.cout},
+                     w.e16 + b * (bl.v->split_bytes / 16), w.eexp + b * 32,
+                     PlainWeights{w.w8 + b * 27 * 32 * bl.cb, 32, bl.cb}, w.wc + b * bl.v->cell_wfloats, nullptr, bl.cb,
+                     a.sum_cells ? 2 : 0, w.part};
     e = fused_pass(a, w, bl.v, xin, n_rows, o, bl.K, L, s);
     if (e != hipSuccess) return e;
     int64_t rb = (n * a.cout + 255) / 256;
