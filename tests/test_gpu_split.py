@@ -75,3 +75,60 @@ def test_not_finite(cin, cout, shape, bad):
         ok = fine & (np.abs(want) < 1e30)
         assert np.abs(got[ok] - want[ok]).max(initial=0) <= 1e-4 * np.abs(want[ok]).max(initial=1)
         assert np.allclose(got[fine], want[fine], rtol=1e-4, atol=1e-3)
+
+
+def cuda(a):
+    return torch.from_numpy(a).cuda()
+
+
+def dw64(r, x, dy):
+    return O.conv3_bwd_weight(r, x, dy)[0]
+
+
+@pytest.mark.parametrize("cin,cout", [(32, 32), (32, 16), (16, 32), (16, 16)])
+@pytest.mark.parametrize("shape", range(len(SHAPES)))
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -60, 2.0 ** 50, "rising"])
+def test_weight_gradient(cin, cout, shape, scale):
+    """Unit-voxel blocks in steps that the count does not fill, and scales
+    that fall from block to block (rows growing along the leaf order)."""
+    (p, dims) = SHAPES[shape]
+    g, r = grid(*p, seed=shape, dims=dims)
+    rng = np.random.default_rng(cin * 100 + cout)
+    x = rng.standard_normal((r.n_leaves, cin)).astype(np.float32)
+    dy = rng.standard_normal((r.n_leaves, cout)).astype(np.float32)
+    w = rng.standard_normal((cout, cin, 3, 3, 3)).astype(np.float32)
+    if scale == "rising":
+        ramp = np.exp2(np.floor(np.linspace(-30, 0, r.n_leaves)))[:, None].astype(np.float32)
+        x *= ramp
+        dy *= ramp[::-1] if shape % 2 else ramp
+    else:
+        x *= np.float32(scale)
+        dy *= np.float32(scale)
+    got = oc.conv3x3x3_backward(g, cuda(x), cuda(w), cuda(dy), need_input=False, need_bias=False)[1].cpu().numpy()
+    want = dw64(r, x, dy)
+    # Bound: as for the layer, 8 units of the sum of the terms' magnitudes
+    # from the splits, and 4 of the fp32 sums; the ramp's small factors meet
+    # values larger by up to 2^30, held to 2^-33 of those: 2^-33 of the
+    # largest |x| and |dy| times the sum of the other's magnitudes.
+    lim = 12 * U32 * dw64(r, np.abs(x), np.abs(dy))
+    lim = lim + 2.0 ** -33 * (dw64(r, np.full_like(x, np.abs(x).max()), np.abs(dy)) +
+                              dw64(r, np.abs(x), np.full_like(dy, np.abs(dy).max())))
+    assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / np.maximum(lim, 1e-300)).max())
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("side", ["x", "dy"])
+def test_weight_gradient_not_finite(bad, side):
+    # Unit voxels alone; the voxel (3, 3, 3) of the tree, away from its sides.
+    g, r = grid(1.0, 1.0, 1.0, seed=1, dims=(1, 1, 1))
+    rng = np.random.default_rng(6)
+    x = rng.standard_normal((r.n_leaves, 32)).astype(np.float32)
+    dy = rng.standard_normal((r.n_leaves, 16)).astype(np.float32)
+    w = np.zeros((16, 32, 3, 3, 3), np.float32)
+    (x if side == "x" else dy)[63, 3] = bad
+    with np.errstate(all="ignore"):
+        want = dw64(r, x, dy).astype(np.float32)
+    got = oc.conv3x3x3_backward(g, cuda(x), cuda(w), cuda(dy), need_input=False, need_bias=False)[1].cpu().numpy()
+    ok = np.isfinite(want) & (np.abs(want) < 1e30)
+    assert (np.isfinite(got) == np.isfinite(want)).all()
+    assert np.abs(got[ok] - want[ok]).max(initial=0) <= 1e-4 * np.abs(want[ok]).max(initial=1)
