@@ -46,6 +46,30 @@ def test_scales(cin, cout, shape, scale):
     assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / np.maximum(lim, 1e-300)).max())
 
 
+@pytest.mark.parametrize("cin,cout", PAIRS)
+@pytest.mark.parametrize("shape", [3])
+@pytest.mark.parametrize("kind", ["row", "channels"])
+def test_range(cin, cout, shape, kind):
+    """No output depends on a value that its sum does not take, or on how one
+    factor is shared between a channel's values and its weights."""
+    (p, dims) = SHAPES[shape]
+    g, r = grid(*p, seed=shape, dims=dims)
+    rng = np.random.default_rng(cin * 100 + cout)
+    x = rng.standard_normal((r.n_leaves, cin)).astype(np.float32)
+    w = (rng.standard_normal((cout, cin, 3, 3, 3)) / np.sqrt(27 * cin)).astype(np.float32)
+    if kind == "row":
+        x[r.n_leaves // 2] *= np.float32(2.0 ** 40)
+    else:
+        f = np.exp2(rng.integers(-30, 31, cin)).astype(np.float32)
+        x *= f
+        w /= f.reshape(1, -1, 1, 1, 1)
+    got = oc.conv3x3x3(g, torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), impl="mfma").cpu().numpy()
+    want = O.conv3(r, x, w)
+    # Bound: as above.
+    lim = 12 * U32 * O.conv3(r, np.abs(x), np.abs(w))
+    assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / np.maximum(lim, 1e-300)).max())
+
+
 @pytest.mark.parametrize("cin,cout", [(32, 32), (16, 8), (8, 16), (4, 16)])
 @pytest.mark.parametrize("shape", [0, 3])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3e38])
