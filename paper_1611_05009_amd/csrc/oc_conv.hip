@@ -2265,15 +2265,16 @@ __global__ void __launch_bounds__(kCell8Threads) k_conv_cell8t_gemm(
   using Vec = typename VecT<C::VEC>::type;
   using Acc = typename AccT<MS>::type;
   const GP rin = GP::make(in, n_rows);
+  int64_t cnt = meta[0];  // the kind comes first in the lists
+  if (cnt > ccap) cnt = ccap;
+  if (cnt > n_leaves) cnt = n_leaves;
+  const WaveTiles wt = wave_tiles((cnt + MS - 1) / MS);
+  if (wt.first - (int)(threadIdx.x >> 6) >= wt.end) return;  // no tile for the workgroup: no weights either
   extern __shared__ float smem[];
   float* wl = smem;
   weights_to_lds<CIN, NT, MS>(wm, wl);
   const int lane = threadIdx.x & 63;
   const int m = lane % MS, g = lane / MS, col = lane % MS;
-  int64_t cnt = meta[0];  // the kind comes first in the lists
-  if (cnt > ccap) cnt = ccap;
-  if (cnt > n_leaves) cnt = n_leaves;
-  const WaveTiles wt = wave_tiles((cnt + MS - 1) / MS);
   float bvals[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -2442,8 +2443,8 @@ __global__ void k_mfma_weights(const float* __restrict__ w, int cout, float* __r
 // ---------------------------------------------------------------------------
 // Instantiated channel pairs.
 // ---------------------------------------------------------------------------
-typedef void (*UnitFn)(int64_t, const int32_t*, const int64_t*, const float*, const u32x4*, const int32_t*,
-                       PlainWeights, uint32_t, const float*, int, int, float*);
+typedef void (*UnitFn)(int64_t, const int32_t*, const int64_t*, const float*, const u32x4*, PlainWeights,
+                       uint32_t, const float*, int, int, float*);
 typedef void (*CellFn)(const uint32_t*, const int64_t*, int, int, int, int64_t, const uint64_t*,
                        const int32_t*, const int64_t*, int, const int32_t*, const float*, const int64_t*,
                        int64_t, int64_t, const float*, const float*, uint32_t, const float*, int, int, float*,
@@ -2454,16 +2455,16 @@ typedef void (*Cell8Fn)(int64_t, const int32_t*, const int64_t*, const int32_t*,
 typedef void (*Cell2Fn)(int64_t, const int32_t*, const int32_t*, const int32_t*, int64_t, const int64_t*,
                         const float*, const float*, uint32_t, const float*, int, int, float*);
 typedef void (*EffWeightFn)(const float*, int, int, float*);
-typedef void (*SplitWeightFn)(const float*, int, int, int, int, u32x4*, int32_t*);
+typedef void (*SplitWeightFn)(const float*, int, u32x4*);
 typedef void (*SumFn)(const uint32_t*, const int64_t*, const int32_t*, const int64_t*,
                       const int64_t*, int64_t, int64_t, const float*, uint32_t, float*,
                       const int64_t*, const int64_t*, int64_t, int64_t, const uint32_t*);
 
 struct MfmaVariant {
   int cin, cout_max, cout_min;
-  size_t split_bytes;      // the unit-voxel kernel's weights
+  int split_vecs;          // the unit-voxel kernel's weights (16-byte vectors)
   int unit_smem;           // its LDS bytes
-  int unit_per_cu;         // and workgroups per CU
+  int unit_threads, unit_per_cu;  // and threads per workgroup, workgroups per CU
   SplitWeightFn split_weights;
   size_t eff_wfloats;      // edge-8 effective weights (MS-row tiles)
   EffWeightFn eff_weights;
@@ -2499,8 +2500,9 @@ MfmaVariant make_variant(int cout_min) {
   v.cin = CIN;
   v.cout_max = 16 * CNT;
   v.cout_min = cout_min;
-  v.split_bytes = SplitCfg<CIN>::WBYTES;
+  v.split_vecs = SplitCfg<CIN>::WVECS;
   v.unit_smem = SplitCfg<CIN>::SMEM;
+  v.unit_threads = SplitCfg<CIN>::THREADS;
   v.unit_per_cu = SplitCfg<CIN>::PER_CU;
   v.split_weights = &k_split_weights<CIN>;
   v.eff_wfloats = MfmaCfg<CIN, NT, MS>::WFLOATS;
@@ -2661,7 +2663,7 @@ size_t smem_limit() {
 // Workspace layout (each part 256-byte aligned):
 //   leaf_info  u64 [n_leaves]                written by execute, for the generic and GEMM paths
 //   wt         f32 [27 cin cout]            generic-kernel weights
-//   u16, uexp  [variant split_bytes], i32 [32]  split weights of the unit-voxel kernel (if a variant exists)
+//   u16        u32x4 [variant split_vecs]   split weights of the unit-voxel kernel (if a variant exists)
 //   wc         f32 [variant cell_wfloats]   cell kernels' B operands
 //   w8         f32 [variant eff_wfloats]    edge-8 effective weights, B operands
 //   6 x (scan workspace (n_trees), i64 [n_trees + 1])
@@ -2696,7 +2698,6 @@ struct ConvWs {
   uint64_t* info;
   float* wt;
   u32x4* u16;
-  int32_t* uexp;
   float* wc;
   float* w8;
   char* scan[kScans];
@@ -2753,8 +2754,7 @@ ConvWs carve(void* base, int64_t n_trees, int64_t n_leaves, int cin, int cout, i
   if (!v) v = bl.v;
   w.info = reinterpret_cast<uint64_t*>(take(sizeof(uint64_t) * (size_t)n_leaves));
   w.wt = reinterpret_cast<float*>(take(sizeof(float) * 27 * (size_t)cin * cout));
-  w.u16 = reinterpret_cast<u32x4*>(take(v ? v->split_bytes * nwl : 0));
-  w.uexp = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * 32 * nwl));
+  w.u16 = reinterpret_cast<u32x4*>(take(v ? sizeof(u32x4) * v->split_vecs * nwl : 0));
   w.wc = reinterpret_cast<float*>(take(v ? sizeof(float) * v->cell_wfloats * nwl : 0));
   w.w8 = reinterpret_cast<float*>(take(v ? sizeof(float) * v->eff_wfloats * nwl : 0));
   for (int k = 0; k < kScans; ++k) {
@@ -2833,7 +2833,6 @@ __global__ void k_zero_u64(unsigned long long* p) { *p = 0ull; }
 // bias still added once).
 struct FusedOut {
   const u32x4* u16;
-  const int32_t* uexp;
   PlainWeights uw;
   const float* wc;
   const float* w8;
@@ -2888,9 +2887,9 @@ hipError_t fused_pass(const oci::ConvArgs& a, const ConvWs& w, const MfmaVariant
                        (const int64_t*)w.pre[1 + k], t0, t1);
     return hipGetLastError();
   };
-  hipLaunchKernelGGL(v->unit[wide], dim3(nblk * v->unit_per_cu, nk), dim3(kSplitThreads), v->unit_smem, s, a.n_leaves,
-                     (const int32_t*)w.nbt, (const int64_t*)(w.pre[0] + a.n_trees), in, o.u16, o.uexp, o.uw, n_rows,
-                     o.bias, o.cout, o.relu, o.out);
+  hipLaunchKernelGGL(v->unit[wide], dim3(nblk * v->unit_per_cu, nk), dim3(v->unit_threads), v->unit_smem, s, a.n_leaves,
+                     (const int32_t*)w.nbt, (const int64_t*)(w.pre[0] + a.n_trees), in, o.u16, o.uw, n_rows, o.bias,
+                     o.cout, o.relu, o.out);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(v->cell8g[wide], dim3(nblk, nk), dim3(kCell8Threads), gsm, s, a.n_leaves,
@@ -3015,8 +3014,8 @@ hipError_t launch_conv_prepare(const ConvArgs& a, void* ws, hipStream_t s) {
                        s, wsrc, wcout, w.wc);
     hipLaunchKernelGGL(v->eff_weights, dim3((unsigned)((v->eff_wfloats + 255) / 256), nb), dim3(256), 0, s,
                        wsrc, wcout, 8, w.w8);
-    hipLaunchKernelGGL(v->split_weights, dim3(28, nb), dim3(256), 0, s, (const float*)w.wt, a.cin, a.cout,
-                       a.cout / wcout, wcout, w.u16, w.uexp);
+    hipLaunchKernelGGL(v->split_weights, dim3((unsigned)((v->split_vecs + 255) / 256), nb), dim3(256), 0, s,
+                       wsrc, wcout, w.u16);
   }
   const unsigned tb = (unsigned)((a.n_trees + 255) / 256);
   hipLaunchKernelGGL(k_leaf_kinds, dim3(tb), dim3(256), 0, s, a.trees, a.n_trees, a.gd, a.gh, a.gw,
@@ -3113,7 +3112,7 @@ hipError_t launch_conv_execute(const ConvArgs& a, void* ws, int impl, hipStream_
   if (e != hipSuccess) return e;
   const int num_cus = L.num_cus;
   if (v != nullptr) {
-    const FusedOut o{w.u16,  w.uexp, PlainWeights{w.wt, a.cin, a.cout}, w.wc, w.w8,
+    const FusedOut o{w.u16,  PlainWeights{w.wt, a.cin, a.cout}, w.wc, w.w8,
                      a.bias, a.cout, a.relu | (a.sum_cells ? 2 : 0), a.out};
     return fused_pass(a, w, v, a.in, n_rows, o, 1, L, s);
   }
@@ -3133,7 +3132,7 @@ hipError_t launch_conv_execute(const ConvArgs& a, void* ws, int impl, hipStream_
     }
     // The K output blocks of input block j in one grid (rows k).
     const size_t b = (size_t)j * bl.K;
-    const FusedOut o{w.u16 + b * (bl.v->split_bytes / 16), w.uexp + b * 32,
+    const FusedOut o{w.u16 + b * bl.v->split_vecs,
                      PlainWeights{w.wt + (size_t)j * 32 * a.cout, a.cin, a.cout},
                      w.wc + b * bl.v->cell_wfloats, w.w8 + b * bl.v->eff_wfloats, nullptr, bl.cb,
                      a.sum_cells ? 2 : 0, w.part};

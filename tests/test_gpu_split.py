@@ -1,6 +1,6 @@
-"""The split fp16 contractions (unit voxels, edge-8 cells with unsplit
-neighbours): partial tiles, scales far from one, values that differ by orders
-of magnitude between places, infinities and NaN, against the oracle."""
+"""The contraction of unit voxels from split terms and that of edge-8 cells
+with unsplit neighbours: partial tiles, scales far from one, values that differ
+by orders of magnitude between places, infinities and NaN, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -18,8 +18,14 @@ def grid(p_root, p_d1, p_d2, seed, dims):
     return oc.from_trees(torch.from_numpy(trees.view(np.int32)).cuda(), 1, *dims), O.make_grid(trees, 1, *dims)
 
 
+def cuda(a):
+    return torch.from_numpy(a).cuda()
+
+
 # All unit voxels (64 groups a tree), few of them (partial tiles), none.
-SHAPES = [((1.0, 1.0, 1.0), (1, 1, 1)), ((1.0, 0.2, 0.1), (1, 2, 1)), ((0.1, 0.1, 0.1), (3, 3, 4)), ((0, 0, 0), (2, 3, 5))]
+SHAPES = [((1.0, 1.0, 1.0), (1, 1, 1)), ((1.0, 0.2, 0.1), (1, 2, 1)), ((0.1, 0.1, 0.1), (3, 3, 4)), ((0, 0, 0), (2, 3, 5)),
+          ((0.5, 0.5, 0.3), (2, 3, 2))]
+GROUPS = [64, 2, 0, 0, 41]  # of 8 unit voxels; a tile takes 4
 PAIRS = [(32, 32), (32, 5), (16, 20), (16, 16), (8, 16), (8, 32), (4, 16), (4, 18), (64, 32)]
 
 
@@ -39,15 +45,25 @@ def test_scales(cin, cout, shape, scale):
         x *= np.float32(scale)
     got = oc.conv3x3x3(g, torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), impl="mfma").cpu().numpy()
     want = O.conv3(r, x, w)
-    # Bound: x and w rounded to 23 bits (2^-23 of a product each) and the
-    # product of their remainders left out (2^-22) make 8 units of the sum of
-    # the terms' magnitudes, the fp32 sums another 4 (the cells' own included).
+    # Bound: the products of small terms left out make 1 unit of the sum of the
+    # terms' magnitudes, the fp32 sums another 11 (the cells' own included).
     lim = 12 * U32 * O.conv3(r, np.abs(x), np.abs(w))
     assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / np.maximum(lim, 1e-300)).max())
 
 
+def unit_groups(r):
+    """Groups of 8 unit voxels: the depth-2 bits (9 to 72) of each tree."""
+    words = np.ascontiguousarray(r.trees).view(np.uint8).reshape(len(r.trees), -1)
+    return int(np.unpackbits(words, axis=1, bitorder="little")[:, 9:73].sum())
+
+
+def test_shapes():
+    for shape, (p, dims) in enumerate(SHAPES):
+        assert unit_groups(grid(*p, seed=shape, dims=dims)[1]) == GROUPS[shape]
+
+
 @pytest.mark.parametrize("cin,cout", PAIRS)
-@pytest.mark.parametrize("shape", [3])
+@pytest.mark.parametrize("shape", [0, 3, 4])
 @pytest.mark.parametrize("kind", ["row", "channels"])
 def test_range(cin, cout, shape, kind):
     """No output depends on a value that its sum does not take, or on how one
@@ -68,6 +84,20 @@ def test_range(cin, cout, shape, kind):
     # Bound: as above.
     lim = 12 * U32 * O.conv3(r, np.abs(x), np.abs(w))
     assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / np.maximum(lim, 1e-300)).max())
+
+
+@pytest.mark.parametrize("cin,cout", [(32, 32), (16, 20), (8, 8), (4, 16)])
+def test_many_tiles(cin, cout):
+    """Several tiles per workgroup, the last one partial."""
+    g, r = grid(1.0, 0.95, 0.95, seed=7, dims=(6, 6, 6))
+    rng = np.random.default_rng(cin)
+    x = rng.standard_normal((r.n_leaves, cin)).astype(np.float32)
+    w = (rng.standard_normal((cout, cin, 3, 3, 3)) / np.sqrt(27 * cin)).astype(np.float32)
+    b = rng.standard_normal(cout).astype(np.float32)
+    got = oc.conv3x3x3(g, cuda(x), cuda(w), cuda(b), relu=True, impl="mfma").cpu().numpy()
+    want = O.conv3(r, x, w, b, relu=True)
+    lim = 12 * U32 * O.conv3(r, np.abs(x), np.abs(w), np.abs(b))
+    assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / lim).max())
 
 
 @pytest.mark.parametrize("cin,cout", [(32, 32), (16, 8), (8, 16), (4, 16)])
@@ -99,10 +129,6 @@ def test_not_finite(cin, cout, shape, bad):
         ok = fine & (np.abs(want) < 1e30)
         assert np.abs(got[ok] - want[ok]).max(initial=0) <= 1e-4 * np.abs(want[ok]).max(initial=1)
         assert np.allclose(got[fine], want[fine], rtol=1e-4, atol=1e-3)
-
-
-def cuda(a):
-    return torch.from_numpy(a).cuda()
 
 
 def dw64(r, x, dy):
