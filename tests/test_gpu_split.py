@@ -1,5 +1,5 @@
-"""The contraction of unit voxels from split terms and that of edge-8 cells
-with unsplit neighbours: partial tiles, scales far from one, values that differ
+"""The contraction of unit voxels from split terms, that of edge-8 cells with
+unsplit neighbours and the weight gradient of unit voxels: partial tiles, scales far from one, values that differ
 by orders of magnitude between places, infinities and NaN, against the oracle."""
 import numpy as np
 import pytest
@@ -139,8 +139,8 @@ def dw64(r, x, dy):
 @pytest.mark.parametrize("shape", range(len(SHAPES)))
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** -60, 2.0 ** 50, "rising"])
 def test_weight_gradient(cin, cout, shape, scale):
-    """Unit-voxel blocks in steps that the count does not fill, and scales
-    that fall from block to block (rows growing along the leaf order)."""
+    """Unit-voxel blocks in steps that the count does not fill, and rows that
+    grow along the leaf order."""
     (p, dims) = SHAPES[shape]
     g, r = grid(*p, seed=shape, dims=dims)
     rng = np.random.default_rng(cin * 100 + cout)
@@ -156,13 +156,33 @@ def test_weight_gradient(cin, cout, shape, scale):
         dy *= np.float32(scale)
     got = oc.conv3x3x3_backward(g, cuda(x), cuda(w), cuda(dy), need_input=False, need_bias=False)[1].cpu().numpy()
     want = dw64(r, x, dy)
-    # Bound: as for the layer, 8 units of the sum of the terms' magnitudes
-    # from the splits, and 4 of the fp32 sums; the ramp's small factors meet
-    # values larger by up to 2^30, held to 2^-33 of those: 2^-33 of the
-    # largest |x| and |dy| times the sum of the other's magnitudes.
+    # Bound: fp32 products and sums, 12 units of the sum of the terms' magnitudes.
     lim = 12 * U32 * dw64(r, np.abs(x), np.abs(dy))
-    lim = lim + 2.0 ** -33 * (dw64(r, np.full_like(x, np.abs(x).max()), np.abs(dy)) +
-                              dw64(r, np.abs(x), np.full_like(dy, np.abs(dy).max())))
+    assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / np.maximum(lim, 1e-300)).max())
+
+
+@pytest.mark.parametrize("cin,cout", [(32, 32), (32, 16), (16, 32), (16, 16)])
+@pytest.mark.parametrize("kind", ["channels", "row", "many"])
+def test_weight_gradient_range(cin, cout, kind):
+    """No weight's gradient depends on values that its sum does not take: other
+    channels' (by 2^60), or a row whose neighbours have no gradient; several
+    blocks per workgroup."""
+    g, r = grid(1.0, 1.0, 0.9, seed=3, dims=(1, 1, 4) if kind == "channels" else (6, 6, 5))
+    rng = np.random.default_rng(cin * 100 + cout)
+    x = rng.standard_normal((r.n_leaves, cin)).astype(np.float32)
+    dy = rng.standard_normal((r.n_leaves, cout)).astype(np.float32)
+    w = np.zeros((cout, cin, 3, 3, 3), np.float32)
+    if kind == "row":
+        x[r.prefix[1] // 2] *= np.float32(2.0 ** 40)  # of the first tree
+        for t in (0, 1, 5, 6, 30, 31, 35, 36):  # it and its neighbours
+            dy[r.prefix[t]:r.prefix[t + 1]] = 0
+    else:
+        x *= np.exp2(rng.integers(-30, 31, cin)).astype(np.float32)
+        dy *= np.exp2(rng.integers(-30, 31, cout)).astype(np.float32)
+    got = oc.conv3x3x3_backward(g, cuda(x), cuda(w), cuda(dy), need_input=False, need_bias=False)[1].cpu().numpy()
+    want = dw64(r, x, dy)
+    # Bound: as above.
+    lim = 12 * U32 * dw64(r, np.abs(x), np.abs(dy))
     assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / np.maximum(lim, 1e-300)).max())
 
 
