@@ -576,10 +576,6 @@ template <> struct AccT<16> { typedef float __attribute__((ext_vector_type(4))) 
 template <int MS>
 __device__ __forceinline__ typename AccT<MS>::type mfma(float a, float b, typename AccT<MS>::type c);
 template <>
-__device__ __forceinline__ AccT<32>::type mfma<32>(float a, float b, AccT<32>::type c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-template <>
 __device__ __forceinline__ AccT<16>::type mfma<16>(float a, float b, AccT<16>::type c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
@@ -2232,192 +2228,6 @@ __global__ void __launch_bounds__(kCellrThreads) k_conv_cellr_mfma(
                                                       kpre, t0, t1);
 }
 
-constexpr int kCell8Threads = 512;
-// Terms of gathered rows in flight: more where a lane's piece of a row is
-// small (at most 2 floats), since those layers wait for the gathers and not
-// for the matrix unit.
-template <int CIN, int MS>
-constexpr int cell8_prefetch() {
-  return CIN / (MS == 32 ? 2 : 4) <= 2 ? 8 : 2;
-}
-
-// Edge-8 cells whose face and edge neighbour trees are unsplit.  Every shell
-// region is then one leaf's row (corners always are), so
-// S_delta = sum_r w(delta, r) x_r over the cell's own row (r = 13) and its 26
-// region rows, w(delta, r) being the number of region r's voxels in the
-// window of delta, and Eq. 8 becomes out = b + sum_r W8_r x_r with effective
-// weights W8_r = (1/512) sum_delta w(delta, r) W[1 - delta], formed once per
-// weight set.  That is a gather-GEMM (K = 27 cin): MS cells
-// per tile, term r's rows gathered into the A operand two terms ahead, the
-// next tile's term rows loaded during this one.
-template <int CIN, int NT, int MS, class GP>
-__global__ void __launch_bounds__(kCell8Threads) k_conv_cell8t_gemm(
-    int64_t n_leaves, const int32_t* __restrict__ brow, const int64_t* __restrict__ meta,
-    const int32_t* __restrict__ codes, int64_t ccap, const float* __restrict__ in,
-    const float* __restrict__ wm, uint32_t n_rows, const float* __restrict__ bias, int cout,
-    int relu, float* __restrict__ out) {
-  // Channel blocks: blockIdx.y selects an output block (its weight layout
-  // and its [n_leaves][cout] destination).
-  wm += (int64_t)blockIdx.y * MfmaCfg<CIN, NT, MS>::WFLOATS;
-  out += (int64_t)blockIdx.y * n_leaves * cout;
-  if (bias != nullptr) bias += (int64_t)blockIdx.y * cout;
-  using C = MfmaCfg<CIN, NT, MS>;
-  using Vec = typename VecT<C::VEC>::type;
-  using Acc = typename AccT<MS>::type;
-  const GP rin = GP::make(in, n_rows);
-  int64_t cnt = meta[0];  // the kind comes first in the lists
-  if (cnt > ccap) cnt = ccap;
-  if (cnt > n_leaves) cnt = n_leaves;
-  const WaveTiles wt = wave_tiles((cnt + MS - 1) / MS);
-  if (wt.first - (int)(threadIdx.x >> 6) >= wt.end) return;  // no tile for the workgroup: no weights either
-  extern __shared__ float smem[];
-  float* wl = smem;
-  weights_to_lds<CIN, NT, MS>(wm, wl);
-  const int lane = threadIdx.x & 63;
-  const int m = lane % MS, g = lane / MS, col = lane % MS;
-  float bvals[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int co = MS * nt + col;
-    bvals[nt] = (bias != nullptr && co < cout) ? bias[co] : 0.f;
-  }
-  // Term rows of the lane's cell in tile t (-1: none).
-  int32_t trow[27];
-  auto stage_load = [&](int64_t t) {
-    const int64_t idx = t * MS + m;
-    const bool ok = t < wt.end && idx < cnt;
-#pragma unroll
-    for (int r = 0; r < 27; ++r) {
-      int32_t v = -1;
-      if (ok) v = r == 13 ? brow[idx] : codes[(int64_t)(r - (r > 13)) * ccap + idx];
-      trow[r] = v < n_leaves ? v : -1;  // only a non-canonical structure exceeds
-    }
-  };
-  auto store_tile = [&](const Acc (&res)[NT], int srow) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int co = MS * nt + col;
-#pragma unroll
-      for (int r = 0; r < (MS == 32 ? 16 : 4); ++r) {
-        const int i = MS == 32 ? 8 * (r / 4) + 4 * g + (r % 4) : 4 * g + r;
-        const int rowi = __shfl(srow, i, 64);
-        if (rowi < 0 || co >= cout) continue;
-        float v = fmaf(res[nt][r], (relu & 2) ? 512.f : 1.f, bvals[nt]);
-        if (relu & 1) v = fmaxf(v, 0.f);
-        out[(int64_t)rowi * cout + co] = v;
-      }
-    }
-  };
-  constexpr int PD = cell8_prefetch<CIN, MS>();
-  static_assert(27 % (PD + 1) == 0, "the gather ring must line up across tiles");
-  Vec abuf[PD + 1][C::NV];
-  const uint32_t coff = 4u * C::VEC * g;  // the lane's first channel, in bytes
-  auto gather_row = [&](uint32_t row, Vec* a) {
-#pragma unroll
-    for (int v = 0; v < C::NV; ++v) a[v] = gather_at<C::VEC>(rin, row, coff + 4 * C::VSTRIDE * v);
-  };
-  uint32_t aoff[27];
-  auto offsets = [&]() {
-#pragma unroll
-    for (int r = 0; r < 27; ++r) aoff[r] = GP::addr(trow[r]);
-  };
-  Acc pacc[NT];
-  int psrow = -1;
-  bool have_prev = false;
-  stage_load(wt.first);
-  offsets();
-#pragma unroll
-  for (int k = 0; k < PD; ++k) gather_row(aoff[k], abuf[k]);
-  for (int64_t tile = wt.first; tile < wt.end; tile += wt.stride) {
-    const int srow = trow[13];
-    Vec bbuf[2][NT][C::NV];
-    auto load_b = [&](int dl, Vec (*b)[C::NV]) {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const Vec* bsrc = reinterpret_cast<const Vec*>(wl) + ((dl * NT + nt) * C::NV) * 64 + lane;
-#pragma unroll
-        for (int v = 0; v < C::NV; ++v) b[nt][v] = bsrc[v * 64];
-      }
-    };
-    Acc acc[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int r = 0; r < (MS == 32 ? 16 : 4); ++r) acc[nt][r] = 0.f;
-    load_b(0, bbuf[0]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int dl = 0; dl < 27; ++dl) {
-      if (dl + PD < 27) gather_row(aoff[dl + PD], abuf[(dl + PD) % (PD + 1)]);
-      else gather_row(aoff[dl + PD - 27], abuf[(dl + PD) % (PD + 1)]);  // next tile
-      if (dl + 1 < 27) load_b(dl + 1, bbuf[(dl + 1) % 2]);
-      if (dl == 3) stage_load(tile + wt.stride);
-      if (dl == 4 && have_prev) store_tile(pacc, psrow);
-      if (dl == 22) {
-        // The next tile's offsets (this tile's are no longer needed past
-        // the gathers already issued).
-#pragma unroll
-        for (int k = 0; k < PD; ++k) aoff[k] = GP::addr(trow[k]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int v = 0; v < C::NV; ++v)
-#pragma unroll
-          for (int e = 0; e < C::VEC; ++e)
-            acc[nt] = mfma<MS>(vget<C::VEC>(abuf[dl % (PD + 1)][v], e),
-                               vget<C::VEC>(bbuf[dl % 2][nt][v], e), acc[nt]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) pacc[nt] = acc[nt];
-    psrow = srow;
-    have_prev = true;
-    offsets();  // the next tile's
-  }
-  if (have_prev) store_tile(pacc, psrow);
-}
-
-// Effective weights of the edge-8 gather-GEMM, in B-operand order (below): term r (region dir = (r/9 - 1, (r/3)%3 - 1, r%3 - 1), r = 13 the cell
-// itself) takes (1/sz^3) sum_delta w(delta, r) W[tap 1 - delta], where
-// w(delta, r) = 0 unless delta_a = dir_a wherever dir_a != 0, and is the
-// product of sz - |delta_a| over the other axes.
-template <int CIN, int NT, int MS>
-__global__ void k_eff_weights(const float* __restrict__ w, int cout, int sz,
-                              float* __restrict__ wm) {
-  using C = MfmaCfg<CIN, NT, MS>;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= C::WFLOATS) return;
-  // Channel blocks: blockIdx.y selects a [cout][CIN][27] weight block.
-  w += (int64_t)blockIdx.y * cout * CIN * 27;
-  wm += (int64_t)blockIdx.y * C::WFLOATS;
-  int q = idx;
-  const int e = q % C::VEC; q /= C::VEC;
-  const int lane = q % 64; q /= 64;
-  const int jv = q % C::NV; q /= C::NV;
-  const int nt = q % NT; q /= NT;
-  const int r = q;
-  const int co = MS * nt + lane % MS;
-  const int ci = C::VEC * (C::KS * jv + lane / MS) + e;
-  if (co >= cout) {
-    wm[idx] = 0.f;
-    return;
-  }
-  const int dir[3] = {r / 9 - 1, (r / 3) % 3 - 1, r % 3 - 1};
-  double acc = 0.0;
-  for (int dl = 0; dl < 27; ++dl) {
-    const int dlt[3] = {dl / 9 - 1, (dl / 3) % 3 - 1, dl % 3 - 1};
-    int wgt = 1;
-    for (int a = 0; a < 3; ++a) {
-      if (dir[a] != 0) wgt *= dlt[a] == dir[a] ? 1 : 0;
-      else wgt *= sz - (dlt[a] != 0 ? 1 : 0);
-    }
-    if (wgt != 0) acc += (double)wgt * (double)w[((int64_t)co * CIN + ci) * 27 + (26 - dl)];
-  }
-  wm[idx] = (float)(acc / ((double)sz * sz * sz));
-}
-
 // Weights in B-operand order: for delta index dl, N-tile nt, vector jv, lane
 // and element e: column co = MS*nt + lane%MS, channel ci = VEC*(KS*jv +
 // lane/MS) + e, tap 26 - dl (Eq. 7 pairs input offset delta with tap 1 - delta).
@@ -2450,24 +2260,21 @@ typedef void (*CellFn)(const uint32_t*, const int64_t*, int, int, int, int64_t, 
                        int64_t, int64_t, const float*, const float*, uint32_t, const float*, int, int, float*,
                        const int64_t*, int64_t, int64_t);
 typedef void (*WeightFn)(const float*, int, float*);
-typedef void (*Cell8Fn)(int64_t, const int32_t*, const int64_t*, const int32_t*, int64_t,
-                        const float*, const float*, uint32_t, const float*, int, int, float*);
+typedef void (*Cell8Fn)(int64_t, const int32_t*, const int64_t*, const int32_t*, int64_t, const float*,
+                        const u32x4*, PlainWeights, uint32_t, const float*, int, int, float*);
 typedef void (*Cell2Fn)(int64_t, const int32_t*, const int32_t*, const int32_t*, int64_t, const int64_t*,
                         const float*, const float*, uint32_t, const float*, int, int, float*);
-typedef void (*EffWeightFn)(const float*, int, int, float*);
-typedef void (*SplitWeightFn)(const float*, int, u32x4*);
+typedef void (*SplitWeightFn)(const float*, const float*, int, u32x4*, u32x4*);
 typedef void (*SumFn)(const uint32_t*, const int64_t*, const int32_t*, const int64_t*,
                       const int64_t*, int64_t, int64_t, const float*, uint32_t, float*,
                       const int64_t*, const int64_t*, int64_t, int64_t, const uint32_t*);
 
 struct MfmaVariant {
   int cin, cout_max, cout_min;
-  int split_vecs;          // the unit-voxel kernel's weights (16-byte vectors)
-  int unit_smem;           // its LDS bytes
-  int unit_threads, unit_per_cu;  // and threads per workgroup, workgroups per CU
+  int split_vecs;          // split weights of a gather-GEMM (16-byte vectors)
+  int unit_smem, cell8g_smem;        // the gather-GEMMs' LDS bytes
+  int split_threads, split_per_cu;   // their threads per workgroup, workgroups per CU
   SplitWeightFn split_weights;
-  size_t eff_wfloats;      // edge-8 effective weights (MS-row tiles)
-  EffWeightFn eff_weights;
   size_t cell_wfloats;     // cell kernels' weights (16-row tiles)
   WeightFn cell_weights;
   // The kernels, [0] gathering through RowsRaw (input below 4 GiB), [1]
@@ -2479,49 +2286,43 @@ struct MfmaVariant {
   Cell8Fn cell8g[2];       // edge-8 cells with unsplit face/edge neighbours
 };
 
-template <int CIN, int NT, int MS, int WIDE>
+template <int CIN, int CNT, int WIDE>
 void set_kernels(MfmaVariant& v) {
-  constexpr int CNT = MfmaCfg<CIN, NT, MS>::NCOL / 16;
   using G = typename std::conditional<WIDE != 0, RowsWide<CIN>, RowsRaw<CIN>>::type;
   v.unit[WIDE] = &k_conv_unit_split<CIN, G>;
   v.cell2[WIDE] = &k_conv_cell2_mfma<CIN, CNT, G>;
   v.cell4[WIDE] = &k_conv_cellr_mfma<CIN, CNT, 4, false, G>;
   v.cell8[WIDE] = &k_conv_cellr_mfma<CIN, CNT, 8, false, G>;
   v.sums[WIDE] = &k_boundary_sums<CIN, G>;
-  v.cell8g[WIDE] = &k_conv_cell8t_gemm<CIN, NT, MS, G>;
+  v.cell8g[WIDE] = &k_conv_cell8t_split<CIN, G>;
 }
 
-// NT, MS: column tiles and tile size of the edge-8 gather-GEMM; CNT: 16-column
-// tiles of the other cell kernels.
-template <int CIN, int NT, int MS>
+// CNT: 16-column tiles of the cell kernels.
+template <int CIN, int CNT>
 MfmaVariant make_variant(int cout_min) {
-  constexpr int CNT = MfmaCfg<CIN, NT, MS>::NCOL / 16;
   MfmaVariant v;
   v.cin = CIN;
   v.cout_max = 16 * CNT;
   v.cout_min = cout_min;
   v.split_vecs = SplitCfg<CIN>::WVECS;
   v.unit_smem = SplitCfg<CIN>::SMEM;
-  v.unit_threads = SplitCfg<CIN>::THREADS;
-  v.unit_per_cu = SplitCfg<CIN>::PER_CU;
+  v.cell8g_smem = Cell8Cfg<CIN>::SMEM;
+  v.split_threads = SplitCfg<CIN>::THREADS;
+  v.split_per_cu = SplitCfg<CIN>::PER_CU;
   v.split_weights = &k_split_weights<CIN>;
-  v.eff_wfloats = MfmaCfg<CIN, NT, MS>::WFLOATS;
-  v.eff_weights = &k_eff_weights<CIN, NT, MS>;
   v.cell_wfloats = MfmaCfg<CIN, CNT, 16>::WFLOATS;
   v.cell_weights = &k_mfma_weights<CIN, CNT, 16>;
-  set_kernels<CIN, NT, MS, 0>(v);
-  set_kernels<CIN, NT, MS, 1>(v);
+  set_kernels<CIN, CNT, 0>(v);
+  set_kernels<CIN, CNT, 1>(v);
   return v;
 }
 
-// cout in [cout_min, cout_max]; 32-wide tiles for cout 17..32, 16-wide ones
-// for cout 1..16 (a tile column past cout holds zero weights and is not
-// stored).
+// cout in [cout_min, cout_max] (a tile column past cout holds zero weights
+// and is not stored).
 const MfmaVariant* find_variant(int cin, int cout) {
   static const MfmaVariant table[] = {
-      make_variant<32, 1, 32>(17), make_variant<16, 1, 32>(17), make_variant<8, 1, 32>(17),
-      make_variant<4, 1, 32>(17),  make_variant<32, 1, 16>(1),  make_variant<16, 1, 16>(1),
-      make_variant<8, 1, 16>(1),   make_variant<4, 1, 16>(1),
+      make_variant<32, 2>(17), make_variant<16, 2>(17), make_variant<8, 2>(17), make_variant<4, 2>(17),
+      make_variant<32, 1>(1),  make_variant<16, 1>(1),  make_variant<8, 1>(1),  make_variant<4, 1>(1),
   };
   for (const MfmaVariant& v : table)
     if (v.cin == cin && cout >= v.cout_min && cout <= v.cout_max) return &v;
@@ -2611,8 +2412,7 @@ constexpr int kSumChunks = OC_SUM_CHUNKS;
 
 // LDS bytes of the widest of a variant's kernels.
 size_t mfma_smem(const MfmaVariant& v) {
-  const size_t eff = sizeof(float) * v.eff_wfloats;
-  const size_t gather = (size_t)v.unit_smem > eff ? (size_t)v.unit_smem : eff;
+  const size_t gather = v.unit_smem > v.cell8g_smem ? v.unit_smem : v.cell8g_smem;
   const size_t cells = sizeof(float) * v.cell_wfloats + (size_t)(kMfmaThreads / 64) * kShell2Lds;
   return gather > cells ? gather : cells;
 }
@@ -2665,7 +2465,8 @@ size_t smem_limit() {
 //   wt         f32 [27 cin cout]            generic-kernel weights
 //   u16        u32x4 [variant split_vecs]   split weights of the unit-voxel kernel (if a variant exists)
 //   wc         f32 [variant cell_wfloats]   cell kernels' B operands
-//   w8         f32 [variant eff_wfloats]    edge-8 effective weights, B operands
+//   w8         f32 [27 cin cout]            edge-8 effective weights, [27][cin][cout] per block
+//   e16        u32x4 [variant split_vecs]   the same, split
 //   6 x (scan workspace (n_trees), i64 [n_trees + 1])
 //              per tree: unit groups, each kind of larger cell, boundary-sum
 //              slots -> prefixes
@@ -2700,6 +2501,7 @@ struct ConvWs {
   u32x4* u16;
   float* wc;
   float* w8;
+  u32x4* e16;
   char* scan[kScans];
   int64_t* pre[kScans];
   int64_t* gkey;
@@ -2756,7 +2558,8 @@ ConvWs carve(void* base, int64_t n_trees, int64_t n_leaves, int cin, int cout, i
   w.wt = reinterpret_cast<float*>(take(sizeof(float) * 27 * (size_t)cin * cout));
   w.u16 = reinterpret_cast<u32x4*>(take(v ? sizeof(u32x4) * v->split_vecs * nwl : 0));
   w.wc = reinterpret_cast<float*>(take(v ? sizeof(float) * v->cell_wfloats * nwl : 0));
-  w.w8 = reinterpret_cast<float*>(take(v ? sizeof(float) * v->eff_wfloats * nwl : 0));
+  w.w8 = reinterpret_cast<float*>(take(v ? sizeof(float) * 27 * (size_t)cin * cout : 0));
+  w.e16 = reinterpret_cast<u32x4*>(take(v ? sizeof(u32x4) * v->split_vecs * nwl : 0));
   for (int k = 0; k < kScans; ++k) {
     w.scan[k] = take(oci::scan_workspace(n_trees));
     w.pre[k] = reinterpret_cast<int64_t*>(take(sizeof(int64_t) * (size_t)(n_trees + 1)));
@@ -2834,8 +2637,9 @@ __global__ void k_zero_u64(unsigned long long* p) { *p = 0ull; }
 struct FusedOut {
   const u32x4* u16;
   PlainWeights uw;
+  const u32x4* e16;
+  PlainWeights ew;
   const float* wc;
-  const float* w8;
   const float* bias;
   int cout, relu;
   float* out;
@@ -2866,11 +2670,8 @@ hipError_t fused_pass(const oci::ConvArgs& a, const ConvWs& w, const MfmaVariant
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(v->unit[wide]),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, v->unit_smem);
   if (e != hipSuccess) return e;
-  // Edge-8 cells with unsplit face and edge neighbours: the gather-GEMM with
-  // effective weights.
-  const size_t gsm = sizeof(float) * v->eff_wfloats;
   e = hipFuncSetAttribute(reinterpret_cast<const void*>(v->cell8g[wide]),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)gsm);
+                          hipFuncAttributeMaxDynamicSharedMemorySize, v->cell8g_smem);
   if (e != hipSuccess) return e;
   auto launch_cells = [&](int k, int64_t t0, int64_t t1) -> hipError_t {
     const size_t smem = wsmem;
@@ -2887,14 +2688,15 @@ hipError_t fused_pass(const oci::ConvArgs& a, const ConvWs& w, const MfmaVariant
                        (const int64_t*)w.pre[1 + k], t0, t1);
     return hipGetLastError();
   };
-  hipLaunchKernelGGL(v->unit[wide], dim3(nblk * v->unit_per_cu, nk), dim3(v->unit_threads), v->unit_smem, s, a.n_leaves,
+  hipLaunchKernelGGL(v->unit[wide], dim3(nblk * v->split_per_cu, nk), dim3(v->split_threads), v->unit_smem, s, a.n_leaves,
                      (const int32_t*)w.nbt, (const int64_t*)(w.pre[0] + a.n_trees), in, o.u16, o.uw, n_rows, o.bias,
                      o.cout, o.relu, o.out);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(v->cell8g[wide], dim3(nblk, nk), dim3(kCell8Threads), gsm, s, a.n_leaves,
+  hipLaunchKernelGGL(v->cell8g[wide], dim3(nblk * v->split_per_cu, nk), dim3(v->split_threads), v->cell8g_smem, s,
+                     a.n_leaves,
                      (const int32_t*)w.brow, (const int64_t*)w.meta, (const int32_t*)w.codes, w.ccap, in,
-                     o.w8, n_rows, o.bias, o.cout, o.relu, o.out);
+                     o.e16, o.ew, n_rows, o.bias, o.cout, o.relu, o.out);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // Edge-2 cells (no boundary sums); the kernel keeps the shell offsets of
@@ -3012,10 +2814,10 @@ hipError_t launch_conv_prepare(const ConvArgs& a, void* ws, hipStream_t s) {
     }
     hipLaunchKernelGGL(v->cell_weights, dim3((unsigned)((v->cell_wfloats + 255) / 256), nb), dim3(256), 0,
                        s, wsrc, wcout, w.wc);
-    hipLaunchKernelGGL(v->eff_weights, dim3((unsigned)((v->eff_wfloats + 255) / 256), nb), dim3(256), 0, s,
-                       wsrc, wcout, 8, w.w8);
-    hipLaunchKernelGGL(v->split_weights, dim3((unsigned)((v->split_vecs + 255) / 256), nb), dim3(256), 0, s,
-                       wsrc, wcout, w.u16);
+    hipLaunchKernelGGL(k_eff_weights, dim3((unsigned)((27 * v->cin * wcout + 255) / 256), nb), dim3(256), 0, s, wsrc,
+                       v->cin, wcout, w.w8);
+    hipLaunchKernelGGL(v->split_weights, dim3((unsigned)((v->split_vecs + 255) / 256), nb, 2), dim3(256), 0, s,
+                       wsrc, (const float*)w.w8, wcout, w.u16, w.e16);
   }
   const unsigned tb = (unsigned)((a.n_trees + 255) / 256);
   hipLaunchKernelGGL(k_leaf_kinds, dim3(tb), dim3(256), 0, s, a.trees, a.n_trees, a.gd, a.gh, a.gw,
@@ -3112,8 +2914,8 @@ hipError_t launch_conv_execute(const ConvArgs& a, void* ws, int impl, hipStream_
   if (e != hipSuccess) return e;
   const int num_cus = L.num_cus;
   if (v != nullptr) {
-    const FusedOut o{w.u16,  PlainWeights{w.wt, a.cin, a.cout}, w.wc, w.w8,
-                     a.bias, a.cout, a.relu | (a.sum_cells ? 2 : 0), a.out};
+    const FusedOut o{w.u16,  PlainWeights{w.wt, a.cin, a.cout}, w.e16,
+                     PlainWeights{w.w8, a.cin, a.cout}, w.wc, a.bias, a.cout, a.relu | (a.sum_cells ? 2 : 0), a.out};
     return fused_pass(a, w, v, a.in, n_rows, o, 1, L, s);
   }
   // Channel blocks: per input block j (copied to a dense [n_leaves][32]
@@ -3134,7 +2936,8 @@ hipError_t launch_conv_execute(const ConvArgs& a, void* ws, int impl, hipStream_
     const size_t b = (size_t)j * bl.K;
     const FusedOut o{w.u16 + b * bl.v->split_vecs,
                      PlainWeights{w.wt + (size_t)j * 32 * a.cout, a.cin, a.cout},
-                     w.wc + b * bl.v->cell_wfloats, w.w8 + b * bl.v->eff_wfloats, nullptr, bl.cb,
+                     w.e16 + b * bl.v->split_vecs,
+                     PlainWeights{w.w8 + b * 27 * 32 * bl.cb, 32, bl.cb}, w.wc + b * bl.v->cell_wfloats, nullptr, bl.cb,
                      a.sum_cells ? 2 : 0, w.part};
     e = fused_pass(a, w, bl.v, xin, n_rows, o, bl.K, L, s);
     if (e != hipSuccess) return e;
