@@ -533,34 +533,25 @@ __device__ __forceinline__ int32_t neighbour_row(const uint32_t* __restrict__ tr
 }
 
 // ---------------------------------------------------------------------------
-// MFMA kernel for unit voxels.
-//
-// A wave owns a tile of MS rows = MS/8 groups.  For a unit voxel the window
-// sum S_delta is the input row of the leaf holding voxel o + delta, so the
-// contraction out = sum_delta W[1-delta] x(o+delta) is an implicit GEMM
-// (M = rows, K = 27 cin, N = cout) whose A rows are gathered from the input.
-//   MS = 32: v_mfma_f32_32x32x2_f32, lane l: A row l%32, k-slot l/32,
-//            B column l%32; D[8(r/4) + 4(l/32) + r%4][l%32] in register r.
-//   MS = 16: v_mfma_f32_16x16x4_f32, lane l: A row l%16, k-slot l/16,
-//            B column l%16; D[4(l/16) + r][l%16] in register r.
+// The fp32 MFMA tile of the cell kernels: 16 rows, v_mfma_f32_16x16x4_f32.
+// Lane l: A row l%16, k-slot l/16, B column l%16; D[4(l/16) + r][l%16] in
+// register r.
 // The K index (delta, ci) is ordered so that a lane of k-slot g holds CH
 // channels of its row in NV vectors of VEC: vector v holds channels
-// VEC (KS v + g) .. + VEC - 1 (KS = k-slots).  One load instruction then
-// reads, per row, KS * VEC consecutive channels, whole 64-byte sectors where
-// the row allows, instead of touching every sector of the row each time.
-// Weights live in LDS already in B-operand order; NT N-tiles of MS columns
+// VEC (4 v + g) .. + VEC - 1.  One load instruction then reads, per row,
+// 4 VEC consecutive channels, whole 64-byte sectors where the row allows,
+// instead of touching every sector of the row each time.
+// Weights live in LDS already in B-operand order; NT N-tiles of 16 columns
 // cover cout (padded with zero weights).
 // ---------------------------------------------------------------------------
-template <int CIN, int NT, int MS>
+template <int CIN, int NT>
 struct MfmaCfg {
-  static constexpr int KS = MS == 32 ? 2 : 4;  // k-slots per MFMA
-  static constexpr int CH = CIN / KS;          // channels per lane per delta
+  static constexpr int KS = 4;         // k-slots per MFMA
+  static constexpr int CH = CIN / KS;  // channels per lane per delta
   static constexpr int VEC = CH % 4 == 0 ? 4 : (CH % 2 == 0 ? 2 : 1);
   static constexpr int NV = CH / VEC;
-  static constexpr int VSTRIDE = KS * VEC;     // channels between a lane's vectors
-  static constexpr int GROUPS = MS / 8;
-  static constexpr int NCOL = MS * NT;
-  static constexpr int WFLOATS = 27 * CIN * NCOL;
+  static constexpr int VSTRIDE = KS * VEC;  // channels between a lane's vectors
+  static constexpr int WFLOATS = 27 * CIN * 16 * NT;
   static_assert(CIN % KS == 0, "cin must split over the k-slots");
 };
 
@@ -721,9 +712,9 @@ __device__ __forceinline__ typename VecT<V>::type gather_at(const G& g, uint32_t
 #define OC_SHELL_GROUP 8
 #endif
 
-template <int CIN, int NT, int MS>
+template <int CIN, int NT>
 __device__ __forceinline__ void weights_to_lds(const float* __restrict__ wm, float* wl) {
-  using C = MfmaCfg<CIN, NT, MS>;
+  using C = MfmaCfg<CIN, NT>;
   typedef float __attribute__((ext_vector_type(4))) f4;
   const f4* src = reinterpret_cast<const f4*>(wm);
   f4* dst = reinterpret_cast<f4*>(wl);
@@ -733,7 +724,7 @@ __device__ __forceinline__ void weights_to_lds(const float* __restrict__ wm, flo
 
 template <int CIN, int NT>
 struct CellCfg {
-  using C = MfmaCfg<CIN, NT, 16>;
+  using C = MfmaCfg<CIN, NT>;
   static constexpr int CH = C::CH;
   static constexpr int VEC = C::VEC;
   static constexpr int VSTRIDE = C::VSTRIDE;
@@ -745,7 +736,7 @@ struct CellCfg {
 // Channels per lane vector of the 16-row cell kernels.
 template <int CIN>
 constexpr int cell_vec() {
-  return MfmaCfg<CIN, 1, 16>::VEC;
+  return MfmaCfg<CIN, 1>::VEC;
 }
 
 // Contract layer JD (deltas 9 JD .. 9 JD + 8) into acc.
@@ -1054,14 +1045,14 @@ __global__ void __launch_bounds__(kMfmaThreads) k_conv_cell2_mfma(
     const float* __restrict__ bias, int cout, int relu, float* __restrict__ out) {
   // Channel blocks: blockIdx.y selects an output block (its weight layout
   // and its [n_leaves][cout] destination).
-  wm += (int64_t)blockIdx.y * MfmaCfg<CIN, NT, 16>::WFLOATS;
+  wm += (int64_t)blockIdx.y * MfmaCfg<CIN, NT>::WFLOATS;
   out += (int64_t)blockIdx.y * n_leaves * cout;
   if (bias != nullptr) bias += (int64_t)blockIdx.y * cout;
   using K = CellCfg<CIN, NT>;
   constexpr int CH = K::CH;
   extern __shared__ float smem[];
   float* wl = smem;
-  weights_to_lds<CIN, NT, 16>(wm, wl);
+  weights_to_lds<CIN, NT>(wm, wl);
   const GP rin = GP::make(in, n_rows);
   const int lane = threadIdx.x & 63;
   int64_t lbeg, lcnt;
@@ -1075,7 +1066,7 @@ __global__ void __launch_bounds__(kMfmaThreads) k_conv_cell2_mfma(
   float bvals[NT];
   bias16<NT>(bias, cout, lane, bvals);
   // The wave's shell offsets: 56 per cell, after the weights.
-  uint32_t* offm = reinterpret_cast<uint32_t*>(smem + MfmaCfg<CIN, NT, 16>::WFLOATS) +
+  uint32_t* offm = reinterpret_cast<uint32_t*>(smem + MfmaCfg<CIN, NT>::WFLOATS) +
                    (threadIdx.x >> 6) * (kShell2Lds / 4) + cl * kShell2Stride;
   // Tiles are pipelined: a tile's row and key are loaded at the start of
   // the tile before it, and its shell table entries halfway through that
@@ -2140,7 +2131,7 @@ __device__ __forceinline__ void cellr_tiles(
     int relu, float* __restrict__ out, const int64_t* __restrict__ kpre, int64_t t0, int64_t t1) {
   // Channel blocks: blockIdx.y selects an output block (its weight layout
   // and its [n_leaves][cout] destination).
-  wm += (int64_t)blockIdx.y * MfmaCfg<CIN, NT, 16>::WFLOATS;
+  wm += (int64_t)blockIdx.y * MfmaCfg<CIN, NT>::WFLOATS;
   out += (int64_t)blockIdx.y * n_leaves * cout;
   if (bias != nullptr) bias += (int64_t)blockIdx.y * cout;
   using K = CellCfg<CIN, NT>;
@@ -2149,7 +2140,7 @@ __device__ __forceinline__ void cellr_tiles(
   constexpr int PV = OC_CELLR_PV < K::NV ? OC_CELLR_PV : K::NV;
   extern __shared__ float smem[];
   float* wl = smem;
-  weights_to_lds<CIN, NT, 16>(wm, wl);
+  weights_to_lds<CIN, NT>(wm, wl);
   const GP rin = GP::make(in, n_rows);
   const GS rs = GS::make(bsum, n_sum_rows);  // the boundary sums, as rows of CIN floats
   const int lane = threadIdx.x & 63;
@@ -2229,11 +2220,11 @@ __global__ void __launch_bounds__(kCellrThreads) k_conv_cellr_mfma(
 }
 
 // Weights in B-operand order: for delta index dl, N-tile nt, vector jv, lane
-// and element e: column co = MS*nt + lane%MS, channel ci = VEC*(KS*jv +
-// lane/MS) + e, tap 26 - dl (Eq. 7 pairs input offset delta with tap 1 - delta).
-template <int CIN, int NT, int MS>
+// and element e: column co = 16*nt + lane%16, channel ci = VEC*(KS*jv +
+// lane/16) + e, tap 26 - dl (Eq. 7 pairs input offset delta with tap 1 - delta).
+template <int CIN, int NT>
 __global__ void k_mfma_weights(const float* __restrict__ w, int cout, float* __restrict__ wm) {
-  using C = MfmaCfg<CIN, NT, MS>;
+  using C = MfmaCfg<CIN, NT>;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= C::WFLOATS) return;
   // Channel blocks: blockIdx.y selects a [cout][CIN][27] weight block.
@@ -2245,8 +2236,8 @@ __global__ void k_mfma_weights(const float* __restrict__ w, int cout, float* __r
   const int jv = r % C::NV; r /= C::NV;
   const int nt = r % NT; r /= NT;
   const int dl = r;
-  const int co = MS * nt + lane % MS;
-  const int ci = C::VEC * (C::KS * jv + lane / MS) + e;
+  const int co = 16 * nt + lane % 16;
+  const int ci = C::VEC * (C::KS * jv + lane / 16) + e;
   wm[idx] = co < cout ? w[((int64_t)co * CIN + ci) * 27 + (26 - dl)] : 0.f;
 }
 
@@ -2310,8 +2301,8 @@ MfmaVariant make_variant(int cout_min) {
   v.split_threads = SplitCfg<CIN>::THREADS;
   v.split_per_cu = SplitCfg<CIN>::PER_CU;
   v.split_weights = &k_split_weights<CIN>;
-  v.cell_wfloats = MfmaCfg<CIN, CNT, 16>::WFLOATS;
-  v.cell_weights = &k_mfma_weights<CIN, CNT, 16>;
+  v.cell_wfloats = MfmaCfg<CIN, CNT>::WFLOATS;
+  v.cell_weights = &k_mfma_weights<CIN, CNT>;
   set_kernels<CIN, CNT, 0>(v);
   set_kernels<CIN, CNT, 1>(v);
   return v;
