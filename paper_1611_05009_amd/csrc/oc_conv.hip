@@ -2637,10 +2637,10 @@ struct FusedOut {
 };
 
 constexpr int kMaxOutBlocks = 8;
-#ifndef OC_BLOCKED_MIN_LEAVES
-#define OC_BLOCKED_MIN_LEAVES 65536
-#endif
-constexpr int64_t kBlockedMinLeaves = OC_BLOCKED_MIN_LEAVES;
+// Leaves from which channel blocks run, and from which for cin >= 128
+// (conv_auto_impl).
+constexpr int64_t kBlockedMinLeaves = 65536;
+constexpr int64_t kBlockedMinLeavesWide = 16384;
 
 // The fused kernels of variant v on input `in` (v->cin channels, n_rows
 // rows) for nk output blocks (grid rows; block k's weight layouts and
@@ -2765,8 +2765,8 @@ bool conv_mfma_supported(int cin, int cout) {
   const MfmaVariant* v = find_variant(cin, cout);
   if (!v) v = conv_blocks(cin, cout).v;
   if (!v) return false;
-  // LDS: the whole weight set plus the neighbourhood rows of every wave must
-  // fit one workgroup (160 KB on gfx950; the device is asked when present).
+  // The widest kernel's LDS must fit one workgroup (160 KB on gfx950; the
+  // device is asked when present).
   return mfma_smem(*v) <= smem_limit();
 }
 
@@ -2775,11 +2775,19 @@ int conv_auto_impl(int64_t n_leaves, int cin, int cout) {
   if (find_variant(cin, cout) != nullptr) return 2;
   // Channel blocks pay Cin/32 passes of six launches each, while the
   // window-sum GEMM writes and re-reads 27 Cin floats per leaf: the GEMM is
-  // faster on small structures unless the input is wide (measured on
-  // 32768 leaves: 64->64 and 64->128 favour the GEMM, 128->64 and 256->128
-  // the blocks; on 4096 leaves the GEMM throughout).
+  // faster on small structures, on fewer leaves the wider the input.  Blocks
+  // against GEMM, ms with the preparation, mixed cells:
+  //   leaves    64->64     64->128    128->64    128->128   256->128
+  //    9.4 k  0.35 0.28  0.42 0.31  0.57 0.39  0.72 0.46  1.31 0.74
+  //   15.6 k  0.35 0.29  0.43 0.33  0.59 0.42  0.75 0.49  1.38 1.22
+  //   20.6 k  0.37 0.34  0.46 0.38  0.62 0.72  0.79 0.80  1.46 1.78
+  //   34.3 k  0.40 0.43  0.51 0.50  0.68 0.81  0.89 0.95  1.66 2.45
+  //   39.5 k  0.41 0.56  0.53 0.64  0.70 1.13  0.93 1.27  1.74 3.05
+  // Below 128 channels the line lies above where the blocks begin to win
+  // (about 35 k leaves): a workspace with fewer boundary-sum slots than the
+  // structure has serves the GEMM, and calls below the line may hold one.
   if (n_leaves >= kBlockedMinLeaves) return 2;
-  return cin >= 128 && n_leaves >= kBlockedMinLeaves / 4 ? 2 : 3;
+  return cin >= 128 && n_leaves >= kBlockedMinLeavesWide ? 2 : 3;
 }
 
 hipError_t launch_conv_prepare(const ConvArgs& a, void* ws, hipStream_t s) {

@@ -86,6 +86,24 @@ def test_range(cin, cout, shape, kind):
     assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / np.maximum(lim, 1e-300)).max())
 
 
+@pytest.mark.parametrize("cin,cout", [(32, 32), (16, 8), (8, 16), (4, 16)])
+@pytest.mark.parametrize("shape", [0, 3])
+def test_smallest_values(cin, cout, shape):
+    """Values of which the last term is below bf16's normal range."""
+    (p, dims) = SHAPES[shape]
+    g, r = grid(*p, seed=shape, dims=dims)
+    rng = np.random.default_rng(cin * 100 + cout)
+    x = (rng.standard_normal((r.n_leaves, cin)) * 2.0 ** -118).astype(np.float32)
+    w = rng.standard_normal((cout, cin, 3, 3, 3)).astype(np.float32)
+    got = oc.conv3x3x3(g, cuda(x), cuda(w), impl="mfma").cpu().numpy()
+    want = O.conv3(r, x, w)
+    # Bound: as above; x is held to 2^-134 (half of bf16's smallest value),
+    # the small products' sums to a few of fp32's (2^-149, 864 of them).
+    ones = np.ones_like(x)
+    lim = 12 * U32 * O.conv3(r, np.abs(x), np.abs(w)) + 2.0 ** -134 * O.conv3(r, ones, np.abs(w)) + 2.0 ** -139
+    assert (np.abs(got - want) <= lim).all(), float((np.abs(got - want) / lim).max())
+
+
 @pytest.mark.parametrize("cin,cout", [(32, 32), (16, 20), (8, 8), (4, 16)])
 def test_many_tiles(cin, cout):
     """Several tiles per workgroup, the last one partial."""
